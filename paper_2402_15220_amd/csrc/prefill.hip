@@ -62,6 +62,7 @@ struct KpfParams {
   float* ws;                    // n_split > 1: one partial per part, [tile][part] of
                                 // kpf_part_floats<D>() floats: O [64][D], then m [64], n [64]
   int32_t* cnt;                 // n_split > 1: arrival counter per tile, zero between launches
+  int cnt_shift;                // counter of tile t is cnt[t << cnt_shift]
   uint32_t ws_bytes;            // bytes of ws (below 4 GiB: 32-bit buffer offsets)
 };
 
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(64 * WPG * NGRP) void kpf_kernel(KpfParams P,
   wait_stores();
   __syncthreads();  // every store of the block's part has completed
   __shared__ int last_part;
-  if (tid == 0) last_part = arrive_last(P.cnt + tix, S);
+  if (tid == 0) last_part = arrive_last(P.cnt + (static_cast<size_t>(tix) << P.cnt_shift), S);
   __syncthreads();
   if (!last_part) return;
   // The last part folds, online over batches of KB parts (Eqn 2 per output
@@ -576,7 +577,7 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
   if (a.n_q <= 0 || a.n_chunks <= 0) return hipSuccess;
   KpfParams P{static_cast<const _Float16*>(a.q), static_cast<_Float16*>(a.o),
               static_cast<const _Float16*>(a.kpool), static_cast<const _Float16*>(a.vpool), a.ss,
-              a.hs, a.n_chunks, a.n_q, a.H, a.C, a.qscale, a.n_split, a.ws, a.cnt,
+              a.hs, a.n_chunks, a.n_q, a.H, a.C, a.qscale, a.n_split, a.ws, a.cnt, a.cnt_shift,
               static_cast<uint32_t>(a.ws_bytes)};
   if (a.n_split < 1 || (a.n_split > 1 && (!a.ws || !a.cnt || a.ws_bytes > 0xFFFFFFF0ull)))
     return hipErrorInvalidValue;

@@ -155,7 +155,7 @@ struct ca_cache {
   std::string patch_error;    // set when such a comparison failed
   int32_t seg_chunks = 0;  // 0: automatic
   int32_t num_cus = 256;
-  int32_t split_chunks = 0;
+  int32_t split_chunks = -1;  // below 0: automatic (schedule 2 only)
   int32_t phase_mask = 7;
   int32_t schedule = 2;  // see ca_set_tuning
   ca::SideStream side;
@@ -222,20 +222,32 @@ struct ca_cache {
         ca::WorkLists full;
         ca::build_tables(tree, &t);
         // patched lists keep the segment size of their last rebuild
-        ca::build_work(tree, t, work.seg_chunks, split_chunks, schedule != 0, cfg.num_heads,
+        ca::build_work(tree, t, work.seg_chunks, split_rule(), schedule != 0, cfg.num_heads,
                        num_cus, &full, schedule == 4, token_head_bytes());
         const char* d = ca::same_work(work, full);
         if (*d) patch_error = std::string("work-list patch differs from a rebuild: ") + d;
       }
     } else {
       ca::build_tables(tree, &tables);
-      ca::build_work(tree, tables, seg_chunks, split_chunks, schedule != 0, cfg.num_heads, num_cus,
-                     &work, schedule == 4, token_head_bytes());
+      auto rebuild = [&](int32_t split) {
+        ca::build_work(tree, tables, seg_chunks, split, schedule != 0, cfg.num_heads, num_cus,
+                       &work, schedule == 4, token_head_bytes());
+      };
+      rebuild(split_rule());
+      // an automatic split adds partials: not past what the static scratch
+      // of ca_attention_noalloc holds, so that no call outgrows it by the split
+      if (work.split_rows > 0 && split_chunks < 0 &&
+          ws_bytes() > ca::kScratchBytes - ca::kScratchCounterBytes)
+        rebuild(0);
     }
     work_valid = true;
     dw_valid = false;
     tree.clear_dirty();
   }
+
+  // The piece length build_work gets: the automatic split belongs to the
+  // default schedule; the others keep rows whole unless told otherwise.
+  int32_t split_rule() const { return split_chunks < 0 && schedule != 2 ? 0 : split_chunks; }
 
   size_t ws_bytes() const {
     const size_t np = static_cast<size_t>(work.n_parts);
@@ -431,7 +443,8 @@ ca_status ca_create(const ca_config* cfg, ca_cache** out) try {
   if (!c) return fail(CA_ERR_HOST, "ca_create: out of host memory");
   c->table_only = cfg->k_pool == nullptr;
   c->seg_chunks = std::max(0, env_int("CA_CF_SEG", 0));
-  c->split_chunks = env_int("CA_SPLIT", 0);
+  const int split = env_int("CA_SPLIT", INT32_MIN);
+  c->split_chunks = split == INT32_MIN ? -1 : std::max(0, split);
   c->schedule = std::min(4, std::max(0, env_int("CA_SCHEDULE", 2)));
   c->check_patches = env_int("CA_CHECK_PATCH", 0) != 0;
   c->prefill_split = std::min(64, std::max(0, env_int("CA_PREFILL_SPLIT", 0)));

@@ -17,6 +17,26 @@ void fill_item_records(WorkLists* w) {
   }
 }
 
+namespace {
+
+// item_of_row: each row's last item (the one decode growth extends). With an
+// explicit piece length (!extend_last) a row in several pieces has none.
+void index_items(WorkLists* w, bool extend_last) {
+  WorkLists& W = *w;
+  const size_t B = W.part_ptr.size() - 1;
+  W.item_of_row.assign(B, -1);
+  std::vector<int32_t> pieces(B, 0);
+  for (size_t i = 0; i < W.items.size(); ++i) {
+    const SfItem& it = W.items[i];
+    int32_t& at = W.item_of_row[it.row];
+    if (pieces[it.row]++ == 0) at = static_cast<int32_t>(i);
+    else if (!extend_last) at = -1;
+    else if (it.ce > W.items[at].ce) at = static_cast<int32_t>(i);
+  }
+}
+
+}  // namespace
+
 void build_tables(const ChunkTree& tree, Tables* out) {
   Tables& T = *out;
   const auto& nodes = tree.nodes();
@@ -215,13 +235,45 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
     run_segs[ru].second = static_cast<int32_t>(W.segs.size()) - run_segs[ru].first;
   }
 
+  // Automatic split of long private lists. One block streams a row's
+  // private chunks of one head at ~36 GB/s, so fewer blocks than compute
+  // units leave HBM idle, and a row much longer than the others ends long
+  // after them. The pieces are as long as one compute unit's share of all
+  // private steps (a step is 64 tokens), at least two steps, at most 64
+  // pieces a row; a row is cut only if that takes at least four steps off
+  // it, about what a piece's partial and the fold of one row cost. More,
+  // shorter pieces were slower: one row of 32,765 tokens (32 heads) takes 460
+  // us whole, 80 us in 8 pieces (256 blocks), 84 in 16, 88 in 32; 8,000
+  // tokens 102 / 24 us, 700 tokens 12.1 us whole and 7.6 in 6 pieces, four
+  // rows of 8,000 124 / 79 us, eight rows of 3,000 (256 blocks) 62.8 whole
+  // and 66.2 in two pieces.
+  constexpr int64_t kMinPieceSteps = 2, kMinSavedSteps = 4, kMaxPieces = 64;
+  const bool auto_split = split_chunks < 0 && partial_items;
+  const int64_t chunk = tree.chunk_size();
+  auto steps_of = [&](int64_t chunks) { return (chunks * chunk + 63) / 64; };
+  int64_t piece_steps = 0;
+  W.split_rows = 0;
+  W.grow_limit = INT32_MAX;
+  if (auto_split) {
+    int64_t total = 0;
+    for (int64_t r = 0; r < B; ++r) total += steps_of(T.priv_ptr[r + 1] - T.priv_ptr[r]);
+    const int64_t cus = num_cus > 0 ? num_cus : 256;
+    piece_steps = std::max(kMinPieceSteps, (total * num_heads + cus - 1) / cus);
+  }
+  if (split_chunks < 0) split_chunks = 0;
+  auto pieces_of = [&](int64_t np) -> int64_t {
+    if (!auto_split) return split_chunks > 0 ? (np + split_chunks - 1) / split_chunks : 1;
+    const int64_t st = steps_of(np);
+    if (st < piece_steps + kMinSavedSteps) return 1;
+    return std::min({(st + piece_steps - 1) / piece_steps, kMaxPieces, np});
+  };
+
   // Sequence-first items and per-row partial lists.
   W.items.clear();
   W.priv_slot.clear();
   W.part_ptr.assign(1, 0);
   W.parts.clear();
   W.mg_rows.clear();
-  (void)tree;
   for (int64_t r = 0; r < B; ++r) {
     // segment partials, root -> leaf: each run met along the path once
     int32_t last_run = -1;
@@ -238,13 +290,18 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
     const int32_t pe = static_cast<int32_t>(W.priv_slot.size());
     const int32_t np = pe - pb;
     const bool has_shared = static_cast<int32_t>(W.parts.size()) > W.part_ptr.back();
-    if (!(partial_items && has_shared) && (split_chunks <= 0 || np <= split_chunks)) {
+    const int64_t pieces = pieces_of(np);
+    if (!(partial_items && has_shared) && pieces <= 1) {
       // the row's own item produces its output directly
       W.items.push_back(SfItem{static_cast<int32_t>(r), pb, pe, -1, 0, 0, 0, 0, {}});
     } else {
       // chunk-first partials and/or several private pieces: every piece
       // writes a partial and the merge epilogue produces the output
-      const int32_t piece = split_chunks > 0 ? split_chunks : std::max(np, 1);
+      int32_t piece = split_chunks > 0 ? split_chunks : std::max(np, 1);
+      if (auto_split && pieces > 1) {
+        piece = static_cast<int32_t>((np + pieces - 1) / pieces);
+        ++W.split_rows;
+      }
       for (int32_t c0 = pb; c0 < pe; c0 += piece) {
         const int32_t c1 = std::min(pe, c0 + piece);
         W.items.push_back(SfItem{static_cast<int32_t>(r), c0, c1, part, 0, 0, 0, 0, {}});
@@ -312,21 +369,25 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
   fill_item_records(&W);
   W.row_of_seq.clear();
   for (int64_t r = 0; r < B; ++r) W.row_of_seq[T.row_seq[r]] = static_cast<int32_t>(r);
-  W.item_of_row.assign(B, -1);
-  std::vector<int32_t> pieces(B, 0);
-  for (size_t i = 0; i < W.items.size(); ++i) {
-    const int32_t r = W.items[i].row;
-    if (pieces[r]++ == 0) W.item_of_row[r] = static_cast<int32_t>(i);
-    else W.item_of_row[r] = -1;
+  index_items(&W, split_chunks <= 0);
+  if (auto_split) {
+    // what patches may add before the split is planned again: twice the
+    // longest item, so rebuilds stay rare against the growth between them
+    int64_t most = (piece_steps + kMinSavedSteps) * 64 / chunk + 1;
+    for (const SfItem& it : W.items) most = std::max<int64_t>(most, it.ce - it.cb);
+    W.grow_limit = static_cast<int32_t>(std::min<int64_t>(2 * most, INT32_MAX));
   }
 }
 
 bool patch_work(const ChunkTree& tree, WorkLists* w) {
   WorkLists& W = *w;
   const auto& grown = tree.grown();
+  std::unordered_map<int32_t, int32_t> more;  // item -> chunks it would gain
   for (const auto& g : grown) {  // check first: all or nothing
     auto it = W.row_of_seq.find(g.first);
     if (it == W.row_of_seq.end() || W.item_of_row[it->second] < 0) return false;
+    const int32_t self = W.item_of_row[it->second];
+    if (W.items[self].ce - W.items[self].cb + ++more[self] > W.grow_limit) return false;
   }
   for (const auto& g : grown) {
     const int32_t r = W.row_of_seq.at(g.first);
@@ -349,7 +410,7 @@ bool patch_work(const ChunkTree& tree, WorkLists* w) {
   std::vector<SfItem> sorted(W.items.size());
   for (size_t i = 0; i < order.size(); ++i) sorted[i] = W.items[order[i]];
   W.items.swap(sorted);
-  for (size_t i = 0; i < W.items.size(); ++i) W.item_of_row[W.items[i].row] = static_cast<int32_t>(i);
+  index_items(&W, true);  // patches run only without an explicit piece length
   fill_item_records(&W);
   return true;
 }
@@ -361,15 +422,21 @@ const char* same_work(const WorkLists& a, const WorkLists& b) {
         a.segs[i].row_begin != b.segs[i].row_begin || a.segs[i].row_end != b.segs[i].row_end ||
         a.segs[i].part_base != b.segs[i].part_base)
       return "segments";
-  if (a.part_ptr != b.part_ptr || a.parts != b.parts || a.mg_rows != b.mg_rows ||
-      a.n_parts != b.n_parts)
-    return "partial lists";
-  if (a.items.size() != b.items.size()) return "item count";
-  auto key = [](const WorkLists& w) {
+  const bool cut = a.split_rows > 0 || b.split_rows > 0;
+  if (!cut) {
+    if (a.part_ptr != b.part_ptr || a.parts != b.parts || a.mg_rows != b.mg_rows ||
+        a.n_parts != b.n_parts)
+      return "partial lists";
+    if (a.items.size() != b.items.size()) return "item count";
+  }
+  auto key = [cut](const WorkLists& w) {
     std::vector<std::vector<int32_t>> k(w.item_of_row.size());
-    for (const auto& it : w.items) {
+    std::vector<SfItem> items = w.items;
+    std::stable_sort(items.begin(), items.end(),
+                     [](const SfItem& x, const SfItem& y) { return x.cb < y.cb; });
+    for (const auto& it : items) {
       auto& v = k[it.row];
-      v.push_back(it.out_part);
+      if (!cut) v.push_back(it.out_part);
       v.insert(v.end(), w.priv_slot.begin() + it.cb, w.priv_slot.begin() + it.ce);
     }
     return k;

@@ -33,7 +33,9 @@ void build_tables(const ChunkTree& tree, Tables* out);
 //    most seg_chunks chunks; the chunk-first kernel handles one (segment,
 //    head, row block) per workgroup and writes one partial per covered row.
 //  * Each row's private chunks form one sequence-first item, or several of
-//    at most split_chunks chunks (split_chunks <= 0 disables splitting).
+//    at most split_chunks chunks (0 disables splitting; below 0: automatic,
+//    rows whose private lists are long against the work of the other rows are
+//    cut so that every compute unit has a piece, see build_work).
 //    An unsplit row is finished by its item (o written directly), which in
 //    the sequential schedule also folds the row's chunk-first partials. With
 //    partial_items (schedules where the chunk-first items run at the same
@@ -56,8 +58,13 @@ struct WorkLists {
   int64_t n_parts = 0;
   int32_t max_seg_rows = 0;
   int32_t seg_chunks = 0;  // segment size used
+  // automatic split: rows cut into pieces, and the longest (in chunks) an
+  // item may grow by patches before the lists are rebuilt
+  int32_t split_rows = 0;
+  int32_t grow_limit = INT32_MAX;
   // for in-place updates: row of each live sequence, and the index in
-  // `items` of each row's single item (-1: none or several pieces)
+  // `items` of each row's last item (-1: none, or several pieces of an
+  // explicit split)
   std::unordered_map<int64_t, int32_t> row_of_seq;
   std::vector<int32_t> item_of_row;
   // serial_reduce only: segments [seg_group_ptr[g], seg_group_ptr[g+1]) are
@@ -85,12 +92,15 @@ void build_work(const ChunkTree& tree, const Tables& t, int32_t seg_chunks, int3
 // paths (tree.grown()): row order, shared runs, segments and partials are
 // unchanged, and each new chunk's slot is appended to its row's private list
 // (the rows after it shift by one). Returns false, changing nothing, when a
-// row cannot be patched this way (no single item for the row).
+// row cannot be patched this way (no item to extend, or the extended item
+// would outgrow grow_limit).
 bool patch_work(const ChunkTree& tree, WorkLists* w);
 
 // Compare two work lists up to the order of sequence-first items: every row
 // has the same private slots and item kind, segments and partial lists are
-// equal. Empty string when they agree, else what differs.
+// equal. Empty string when they agree, else what differs. Where the
+// automatic split cut a row in either list, the pieces (and so the partial
+// lists) may differ and only their concatenation is compared.
 const char* same_work(const WorkLists& a, const WorkLists& b);
 
 }  // namespace ca

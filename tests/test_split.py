@@ -1,0 +1,129 @@
+"""Automatic split of long private lists (the default schedule): the plan,
+seen through the workspace size, decode growth on cut rows, and the results of
+cut rows against the oracle."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+from parity_util import Pair, assert_close
+from paper_2402_15220_amd import binding as B
+
+
+def _align(x, a=256):
+    return (x + a - 1) // a * a
+
+
+def _ws(parts, H, d):
+    return _align(parts * H * d * 4) + _align(parts * H * 2 * 4)
+
+
+def _table_cache(c, H, d, slots=1 << 16, check=False):
+    if check:
+        os.environ["CA_CHECK_PATCH"] = "1"
+    try:
+        return B.ca_create(c, H, d, B.CA_FP16, slots)
+    finally:
+        os.environ.pop("CA_CHECK_PATCH", None)
+
+
+# 256 compute units: a piece is ceil(total steps * H / 256) steps, at least 2;
+# a row is cut when that takes at least 4 steps off it
+@pytest.mark.parametrize("c,H,lens,parts", [
+    (64, 32, [32765], 8),            # 512 steps: pieces of 64
+    (64, 32, [5 * 64], 0),           # 5 steps, pieces of 2: 3 saved, whole
+    (64, 32, [6 * 64], 3),           # 6 steps: 4 saved, 3 pieces
+    (64, 1, [64 * 512], 64),         # 256 pieces of 2 would be over the 64 a row may have
+    (64, 256, [64 * 4096], 0),       # every compute unit has a whole head
+    (16, 32, [32 * 64], 8),          # 128 chunks of 16 are 32 steps: pieces of 4
+    (128, 32, [32 * 64], 8),         # 16 chunks of 128 likewise
+    (64, 32, [64 * 300] + [64] * 8, 8),   # 308 steps: pieces of 39, the long row only
+    (300, 8, [300 * 2], 2),          # more pieces wanted than chunks
+])
+def test_plan(c, H, lens, parts):
+    h = _table_cache(c, H, 64)
+    tok = 0
+    for sid, n in enumerate(lens):
+        B.ca_insert(h, sid, np.arange(tok, tok + n))
+        tok += n
+    assert B.ca_workspace_size(h) == _ws(parts, H, 64)
+    B.ca_set_tuning(h, split_chunks=0)       # an explicit 0 disables it
+    assert B.ca_workspace_size(h) == 0
+    B.ca_destroy(h)
+    h = _table_cache(c, H, 64)
+    B.ca_insert(h, 0, np.arange(lens[0]))
+    B.ca_set_tuning(h, schedule=0)           # other schedules keep rows whole
+    assert B.ca_workspace_size(h) == 0
+    B.ca_destroy(h)
+
+
+@pytest.mark.parametrize("H,rows", [(1, 1), (4, 3), (64, 5)])
+def test_growth_patches_cut_rows(H, rows):
+    """Growth extends a cut row's last piece in place, each patch equal to a
+    rebuild; when the piece has doubled, the row is planned again."""
+    h = _table_cache(2, H, 64, check=True)
+    for sid in range(rows):
+        B.ca_insert(h, sid, np.arange(1000 * sid, 1000 * sid + 900))
+    B.ca_seq_order(h)
+    sizes = {B.ca_workspace_size(h)}
+    for step in range(1200):
+        B.ca_append_batch(h, np.arange(rows), np.full(rows, 7))
+        B.ca_seq_order(h)
+        B.ca_stats(h)
+        sizes.add(B.ca_workspace_size(h))
+    st = B.ca_stats(h)
+    assert st["patches"] > 550               # one per new chunk of every row, few rebuilds
+    assert len(sizes) <= 4
+    B.ca_destroy(h)
+
+
+@pytest.mark.parametrize("H,parts", [(128, 248), (64, 249)])
+def test_static_scratch_never_outgrown_by_the_split(H, parts):
+    """31 rows over 7 segments: 248 partials. With 128 heads they fill the
+    static scratch (16,515,072 bytes) to within one, so the long row stays
+    whole; with 64 heads there is room and it is cut in two."""
+    d = 128
+    h = _table_cache(1, H, d)
+    for sid in range(30):
+        B.ca_insert(h, sid, list(range(64 * 7)) + [10_000 + sid])
+    B.ca_insert(h, 30, list(range(64 * 7)) + [20_000 + i for i in range(3000 if H == 128 else 1500)])
+    B.ca_set_tuning(h, seg_chunks=64)
+    assert B.ca_workspace_size(h) == _ws(parts, H, d)
+    B.ca_destroy(h)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("c,H,d,dt,prompt,lens", [
+    (64, 2, 128, np.float16, 0, [64 * 6 + 1]),
+    (64, 1, 64, np.float16, 0, [64 * 130 + 7]),       # more than 64 pieces wanted
+    (16, 3, 128, np.float16, 40, [1500, 90, 700]),    # a shared prompt: chunk-first partials too
+    (100, 2, 64, np.float32, 0, [2001, 640]),
+    (5, 1, 128, np.float32, 12, [900, 1]),
+    (64, 4, 128, np.float16, 4200, [3000, 2000]),     # more than 64 partials a row (seg 1 below)
+])
+def test_cut_rows_against_the_oracle(c, H, d, dt, prompt, lens):
+    print(f"[case] split c={c} H={H} d={d} {np.dtype(dt).name} prompt={prompt} lens={lens}", flush=True)
+    rng = np.random.default_rng(c * H + d)
+    steps = 40
+    slots = sum(-(-(n + steps) // c) + 2 for n in lens + [prompt])
+    p = Pair(c, H, d, dt, slots)
+    kp = rng.standard_normal((2, prompt, H, d)).astype(dt)
+    for sid, n in enumerate(lens):
+        own = rng.standard_normal((2, n, H, d)).astype(dt)
+        kv = np.concatenate([kp, own], axis=1)
+        p.insert(sid, list(range(prompt)) + [100_000 * (sid + 1) + i for i in range(n)], kv[0], kv[1])
+    if prompt > 4000:
+        p.cache.set_tuning(seg_chunks=1)
+    ids = list(range(len(lens)))
+    for step in range(3):
+        q = {sid: rng.standard_normal((H, d)).astype(dt) for sid in ids}
+        o, qs, row_seq = p.attention(q)
+        assert_close(o, p.reference(row_seq, qs, 0.0), dt, f"step {step}")
+        out = torch.empty(qs.shape, dtype=torch.from_numpy(qs).dtype, device="cuda")
+        o2 = p.cache.attention_noalloc(torch.from_numpy(qs).cuda(), out)
+        torch.cuda.synchronize()
+        assert_close(o2.cpu().numpy(), o, dt, "noalloc")
+        for _ in range(steps // 2 if step < 2 else 0):  # growth patches the last pieces
+            kv = rng.standard_normal((2, len(ids), H, d)).astype(dt)
+            p.append(ids, [7] * len(ids), kv[0], kv[1])

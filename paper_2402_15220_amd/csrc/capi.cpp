@@ -635,7 +635,7 @@ static ca_status launch_attention_call(ca_cache* cache, const void* q, void* o, 
   a.ws_ml = np ? reinterpret_cast<float*>(ws + align_up(o_bytes, 256)) : nullptr;
   a.qscale = sc * 1.4426950408889634f;
   a.cnt = cnt;
-  a.cnt_shift = ca::counter_shift(static_cast<size_t>(cache->tree.num_seqs()) * a.H);
+  a.cnt_layout = ca::counter_layout(static_cast<size_t>(cache->tree.num_seqs()), a.H);
   a.row_map = row_map;
   hipError_t e = ca::launch_attention(a, cache->dw, s, cache->phase_mask, cache->side);
   if (e != hipSuccess) return hip_fail(e, "ca_attention launch");
@@ -665,9 +665,10 @@ static ca_status attention_impl(ca_cache* cache, const void* q, void* o, float s
     row_map = cache->d_rowmap;
   }
   if (cache->schedule == 3 && (st = cache->ensure_side()) != CA_OK) return st;
-  const size_t counters = static_cast<size_t>(cache->tree.num_seqs()) * cache->cfg.num_heads;
   st = ca_cache::ensure_counters(&cache->d_cnt, &cache->d_cnt_cap,
-                                 counters << ca::counter_shift(counters), s);
+                                 ca::counter_entries(static_cast<size_t>(cache->tree.num_seqs()),
+                                                     static_cast<size_t>(cache->cfg.num_heads)),
+                                 s);
   if (st != CA_OK) return st;
   return launch_attention_call(cache, q, o, scale, static_cast<char*>(ws), cache->d_cnt, row_map, s);
 }
@@ -723,7 +724,10 @@ ca_status ca_attention_noalloc(ca_cache* cache, const void* q, void* o, float sc
   // the scratch keeps whatever the last call on this GPU left: the counters
   // are cleared by a kernel on the caller's stream before every call
   hipError_t e = ca::launch_fill_i32(
-      cnt, static_cast<int64_t>(counters << ca::counter_shift(counters)), 0, s);
+      cnt,
+      static_cast<int64_t>(ca::counter_entries(static_cast<size_t>(cache->tree.num_seqs()),
+                                               static_cast<size_t>(cache->cfg.num_heads))),
+      0, s);
   if (e != hipSuccess) return hip_fail(e, "ca_attention_noalloc counter clear");
   return launch_attention_call(cache, q, o, scale, cache->scratch + ca::kScratchCounterBytes, cnt,
                                nullptr, s);
@@ -841,13 +845,13 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
       return st;
     if ((st = ca_cache::ensure_counters(&cache->d_pf_cnt, &cache->d_pf_cnt_cap,
                                         static_cast<size_t>(tiles)
-                                            << ca::counter_shift(static_cast<size_t>(tiles)),
+                                            << ca::tile_counter_shift(static_cast<size_t>(tiles)),
                                         s)) != CA_OK)
       return st;
     a.ws = cache->d_pf_ws;
     a.ws_bytes = ws;
     a.cnt = cache->d_pf_cnt;
-    a.cnt_shift = ca::counter_shift(static_cast<size_t>(tiles));
+    a.cnt_shift = ca::tile_counter_shift(static_cast<size_t>(tiles));
   }
   hipError_t e = ca::launch_prefill(a, s);
   if (e != hipSuccess) return hip_fail(e, "ca_prefill_attention launch");

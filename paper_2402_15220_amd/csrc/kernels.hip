@@ -48,10 +48,10 @@ __device__ __forceinline__ int io_row(const int32_t* row_map, int row) {
   return row_map ? row_map[row] : row;
 }
 
-// Arrival counter of (row, head): counters sit 1 << shift apart (see
-// counter_shift).
-__device__ __forceinline__ int32_t* arrival_counter(int32_t* cnt, int shift, int row, int H, int h) {
-  return cnt + ((static_cast<size_t>(row) * H + h) << shift);
+// Arrival counter of (row, head) in the layout counter_layout() picked.
+__device__ __forceinline__ int32_t* arrival_counter(int32_t* cnt, int layout, int row, int H, int h) {
+  if (layout < 0) return cnt + (static_cast<size_t>(row) * H + h);
+  return cnt + (static_cast<size_t>(row >> layout) * H + h) * 32 + (row & ((1 << layout) - 1));
 }
 
 // Byte offset of element d of partial p, head h in the partial-O workspace.
@@ -264,7 +264,7 @@ struct KsfParams {
   int C;
   float qscale;
   int32_t* cnt;  // partial-writing schedules: per (row, head) arrival counters, else null
-  int cnt_shift; // counter (row, head) is cnt[(row * H + head) << cnt_shift]
+  int cnt_layout;  // see counter_layout()
   const int32_t* row_map;  // tree row -> row of q and o (null: tree order)
 };
 
@@ -485,7 +485,7 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
     // device-scope load, means every other part was visible before it was
     // counted; the branch on it precedes every part load (the compiler
     // fence keeps them there) and those loads are device-scope (DEV = true).
-    int32_t* c = arrival_counter(P.cnt, P.cnt_shift, it.row, H, h);
+    int32_t* c = arrival_counter(P.cnt, P.cnt_layout, it.row, H, h);
     int ready = 0;
     if (lane == 0) ready = __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == np - 1;
     if (__shfl(ready, 0)) {
@@ -517,7 +517,7 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
     // partial-writing schedules: the last contributor of the row finishes it
     wait_stores();
     int last = 0;
-    if (lane == 0) last = arrive_last(arrival_counter(P.cnt, P.cnt_shift, it.row, H, h), np);
+    if (lane == 0) last = arrive_last(arrival_counter(P.cnt, P.cnt_layout, it.row, H, h), np);
     if (__shfl(last, 0))
       finish_row<T, D, true>(P.part_ptr, P.parts, P.ws_o, P.o_bytes, P.ws_ml, P.o, P.row_map, H, it.row, h,
                              lane);
@@ -566,7 +566,7 @@ struct KcfParams {
   // partial-writing schedules only (null otherwise): per (row, head) arrival counters
   // and what the last contributor needs to finish the row
   int32_t* cnt;
-  int cnt_shift;
+  int cnt_layout;
   void* o;
   const int32_t* part_ptr;
   const int32_t* parts;
@@ -629,7 +629,7 @@ __device__ __forceinline__ void cf_arrive(const KcfParams& P, int rb, int nrows,
     int last = 0;
     if (tid < nrows) {
       const int r = rb + tid;
-      last = arrive_last(arrival_counter(P.cnt, P.cnt_shift, r, P.H, h),
+      last = arrive_last(arrival_counter(P.cnt, P.cnt_layout, r, P.H, h),
                          P.part_ptr[r + 1] - P.part_ptr[r]);
     }
     flags[tid] = last;
@@ -1439,10 +1439,10 @@ hipError_t launch_all(const AttnArgs& a, const DevWork& w, hipStream_t s, int ma
   const bool counting = w.schedule == 2 || w.schedule == 3;  // the last contributor finishes each row
   P.cf = KcfParams{a.q, a.kpool, a.vpool, a.ss, a.hs, a.slot_len, w.segs, w.seg_slots, a.ws_o,
                    reinterpret_cast<float2*>(a.ws_ml), a.ws_o_bytes, a.H, a.C, a.qscale,
-                   counting ? a.cnt : nullptr, a.cnt_shift, a.o, w.part_ptr, w.parts, a.row_map};
+                   counting ? a.cnt : nullptr, a.cnt_layout, a.o, w.part_ptr, w.parts, a.row_map};
   P.sf = KsfParams{a.q, a.o, a.kpool, a.vpool, a.ss, a.hs, a.slot_len, w.items, w.priv_slot, w.part_ptr,
                    w.parts, a.ws_o, reinterpret_cast<float2*>(a.ws_ml), a.ws_o_bytes, a.H, a.C,
-                   a.qscale, counting ? a.cnt : nullptr, a.cnt_shift, a.row_map};
+                   a.qscale, counting ? a.cnt : nullptr, a.cnt_layout, a.row_map};
   // At most 16 or 32 covered rows per chunk-first block; wider runs take
   // several row blocks, which re-read the chunk. Their block indices differ
   // by a multiple of H, so for H a multiple of 8 they land on the same XCD

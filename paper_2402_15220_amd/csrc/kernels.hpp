@@ -52,7 +52,7 @@ struct AttnArgs {
   uint32_t ws_o_bytes;  // bytes of the ws_o region (below 4 GiB)
   float qscale;  // softmax scale * log2(e)
   int32_t* cnt;  // [B][H] arrival counters, zero between launches
-  int cnt_shift; // counter i is cnt[i << cnt_shift] (counter_shift)
+  int cnt_layout; // counter_layout(rows, H)
   const int32_t* row_map = nullptr;  // [B] tree row -> row of q and o (null: tree order)
 };
 
@@ -88,7 +88,7 @@ struct PrefillArgs {
   float* ws = nullptr;
   size_t ws_bytes = 0;  // bytes of ws the launch may touch (below 4 GiB)
   int32_t* cnt = nullptr;
-  int cnt_shift = 0;    // counter of tile t is cnt[t << cnt_shift] (counter_shift)
+  int cnt_shift = 0;    // counter of tile t is cnt[t << cnt_shift] (tile_counter_shift)
 };
 constexpr size_t prefill_part_bytes(int D) { return (64 * static_cast<size_t>(D) + 128) * 4; }
 hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream);
@@ -101,17 +101,32 @@ constexpr size_t kScratchBytes = size_t(16) << 20;
 constexpr size_t kScratchCounterBytes = size_t(256) << 10;
 hipError_t scratch_address(char** out);
 
-// log2 of the distance (in int32) between two of n arrival counters: as far
-// apart as kScratchCounterBytes allows, at most one per 128-byte line.
-// Device-scope atomics are performed in memory, one at a time per line at
-// ~40 ns each, so counters packed 32 to a line queue behind each other: one
-// row's 32 heads in 16,384 pieces took 678 us packed and 150 us spread, a
-// batch of 16 ragged rows over a 1024-token prompt 19.8 and 16.3 us.
-constexpr int counter_shift(size_t n) {
-  int s = 0;
-  while (s < 5 && (n << (s + 1)) <= kScratchCounterBytes / sizeof(int32_t)) ++s;
-  return s;
+// Layout of the decode arrival counters, at most kScratchCounterBytes of
+// them unless there are more (row, head) pairs than that. Device-scope atomics
+// are performed in memory, one access at a time per 128-byte line at ~40 ns
+// each, so packed counters (a row's 32 heads in one line) queue behind each
+// other: one row's 32 heads in 16,384 pieces took 678 us packed and 150 us a
+// line each. Layout r >= 0: the counters of 2^r consecutive rows of one head
+// share a line of 32.
+//   0   up to 512 pairs, every counter a line of its own (512 pairs, 16
+//       ragged rows over a 1024-token prompt: 20.1 us packed, 16.2 so, 16.5
+//       with 16 rows a line; 128 pairs: 13.0 / 12.5 / 12.8 us);
+//   4   above: a chunk-first block counts its 16 rows in one or two accesses
+//       (1,024 pairs, the benchmark's tree: 49.5 us packed, 49.2 a line each,
+//       48.8 so; 2,048 pairs on a two-level tree 67.6 / 67.9 / 67.0);
+//   -1  packed, where that would not fit.
+constexpr size_t kScratchCounters = kScratchCounterBytes / sizeof(int32_t);
+constexpr int counter_layout(size_t rows, size_t H) {
+  const int r = rows * H <= 512 ? 0 : 4;
+  return ((rows + (size_t(1) << r) - 1) >> r) * H * 32 <= kScratchCounters ? r : -1;
 }
+// int32 entries the layout takes
+constexpr size_t counter_entries(size_t rows, size_t H) {
+  const int r = counter_layout(rows, H);
+  return r < 0 ? rows * H : ((rows + (size_t(1) << r) - 1) >> r) * H * 32;
+}
+// Prefill tile t's counter is entry t << shift: a line each, where that fits.
+constexpr int tile_counter_shift(size_t tiles) { return tiles * 32 <= kScratchCounters ? 5 : 0; }
 
 // p[0 .. n) = value on `stream` (a kernel, not a memset node).
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t value, hipStream_t stream);

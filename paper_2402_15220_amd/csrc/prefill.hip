@@ -62,7 +62,7 @@ struct KpfParams {
   float* ws;                    // n_split > 1: one partial per part, [tile][part] of
                                 // kpf_part_floats<D>() floats: O [64][D], then m [64], n [64]
   int32_t* cnt;                 // n_split > 1: arrival counter per tile, zero between launches
-  int cnt_shift;                // counter of tile t is cnt[t << cnt_shift]
+  int cnt_shift;                // counter of tile t is cnt[t << cnt_shift] (tile_counter_shift)
   uint32_t ws_bytes;            // bytes of ws (below 4 GiB: 32-bit buffer offsets)
 };
 

@@ -1,7 +1,7 @@
-"""Arrival counters of the partial-writing schedules: their spacing shrinks as
-the number of (row, head) pairs grows (32 apart up to 2,048 pairs, adjacent
-above 32,768); every spacing against the oracle, twice (the kernels reset the
-counters they used)."""
+"""Arrival counters of the partial-writing schedules: a line each up to 512
+(row, head) pairs, 16 rows of a head a line above, packed where that would not
+fit 65,536 entries; every layout against the oracle, twice (the kernels reset
+the counters they used)."""
 import numpy as np
 import pytest
 import torch
@@ -11,8 +11,8 @@ from parity_util import Pair, assert_close
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows,H", [(32, 64), (33, 64), (256, 65), (513, 64)])
-def test_counter_spacings(rows, H):
+@pytest.mark.parametrize("rows,H", [(8, 64), (9, 57), (37, 65), (513, 64), (512, 64)])
+def test_counter_layouts(rows, H):
     print(f"[case] counters rows={rows} H={H}", flush=True)
     d, c = 64, 8
     rng = np.random.default_rng(rows * H)
@@ -24,7 +24,7 @@ def test_counter_spacings(rows, H):
         kv = np.concatenate([kp, own], axis=1)
         p.insert(sid, prompt + [1000 + sid, 1, 2], kv[0], kv[1])
     q = {sid: rng.standard_normal((H, d)).astype(np.float16) for sid in range(rows)}
-    some = sorted(rng.choice(rows, 12, replace=False))
+    some = sorted(rng.choice(rows, min(rows, 12), replace=False))
     for rep in range(2):
         o, qs, row_seq = p.attention(q)
         ref = p.reference(row_seq, qs, 0.0, rows=some)

@@ -687,6 +687,124 @@ __device__ __forceinline__ void cf_arrive(const KcfParams& P, int rb, int nrows,
   for (int e = 0; e < DPT; ++e) out[e] = static_cast<T>(acc[e] * inv);
 }
 
+// End of a chunk-first block: merge the states of its wavefronts (each has
+// m_run, its lane group's share of the row sums n_part, and O^T, which
+// put(t, row, scale) writes rescaled to a row of D floats), write the
+// segment's partial (O, m, n) for every covered row, or fold it into the
+// row's accumulator (serial reduction), and count the arrival. The LDS holds
+// one [R][D + 4] buffer per wavefront and, from byte `big`, the maxima and sums.
+template <typename OUT_T, int D, int NRT, int NCH, typename PUT>
+__device__ __forceinline__ void cf_publish(const KcfParams& P, const CfSeg& sg, int rb, int nrows,
+                                           int h, char* lds, int big, const float (&m_run)[NRT],
+                                           const float (&n_part)[NRT], FinishList& fl, PUT put) {
+  constexpr int R = 16 * NRT;
+  constexpr int NW = 4 * NCH;
+  constexpr int OS = D + 4;  // merge buffer row stride (floats)
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int H = P.H;
+  const int nrt = (nrows + 15) / 16;
+  float* obuf = reinterpret_cast<float*>(lds);
+  float* mbuf = reinterpret_cast<float*>(lds + big);  // [NW][R]
+  float* nbuf = mbuf + NW * R;                        // [NW][R]
+  finish_ids(P, fl);
+  // Merge the wavefront states per row: common max, rescaled sums.
+#pragma unroll
+  for (int t = 0; t < NRT; ++t) {
+    float ns = n_part[t];
+    ns += __shfl_xor(ns, 16);
+    ns += __shfl_xor(ns, 32);
+    if (g == 0) {
+      mbuf[w * R + 16 * t + l16] = m_run[t];
+      nbuf[w * R + 16 * t + l16] = ns;
+    }
+  }
+  __syncthreads();  // all wavefronts are past their loops: the slices are free
+  float scale[NRT], Mrow[NRT], Nrow[NRT];
+#pragma unroll
+  for (int t = 0; t < NRT; ++t) {
+    const int r = 16 * t + l16;
+    float M = kNegBig;
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww) M = fmaxf(M, mbuf[ww * R + r]);
+    float N = 0.f;
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww) N += nbuf[ww * R + r] * fast_exp2(mbuf[ww * R + r] - M);
+    scale[t] = fast_exp2(m_run[t] - M);
+    Mrow[t] = M;
+    Nrow[t] = N;
+  }
+  // every wavefront parks its rescaled O^T in its own buffer ([row][d], one
+  // 16-byte write per tile); the partial stores below add them up
+  {
+    float* mine = obuf + w * (R * OS);
+#pragma unroll
+    for (int t = 0; t < NRT; ++t) {
+      if (t < nrt) {
+        const int r = 16 * t + l16;
+        put(t, mine + r * OS, scale[t]);
+      }
+    }
+  }
+  __syncthreads();
+  // write the segment's partial (O, m, n) for every covered row
+  const size_t pbase = static_cast<size_t>(sg.part_base + (rb - sg.row_begin));
+  const bool fold = sg.pad0 != 0;
+  if (fold) {
+    // serial reduction: fold into the row's accumulator (Eqn 2), which an
+    // earlier launch wrote; per-row factors go through mbuf / nbuf (free now)
+    if (w == 0 && g == 0) {
+#pragma unroll
+      for (int t = 0; t < NRT; ++t) {
+        const int r = 16 * t + l16;
+        if (r < nrows) {
+          const float* pml = reinterpret_cast<const float*>(P.ws_ml + (pbase + r) * H + h);
+          const float mp = ld_dev(pml), np = ld_dev(pml + 1);
+          const float mx = fmaxf(Mrow[t], mp);
+          const float x = fast_exp2(Mrow[t] - mx), y = fast_exp2(mp - mx);
+          mbuf[r] = x;
+          nbuf[r] = y;
+          Mrow[t] = mx;
+          Nrow[t] = x * Nrow[t] + y * np;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  {
+    const __amdgpu_buffer_rsrc_t rs = part_rsrc(P.ws_o, P.o_bytes);
+    for (int e = tid; e < nrows * (D / 4); e += 256 * NCH) {
+      const int r = e / (D / 4), d = 4 * (e % (D / 4));
+      float4 v = *reinterpret_cast<const float4*>(obuf + r * OS + d);
+#pragma unroll
+      for (int ww = 1; ww < NW; ++ww) {
+        const float4 u = *reinterpret_cast<const float4*>(obuf + ww * (R * OS) + r * OS + d);
+        v = make_float4(v.x + u.x, v.y + u.y, v.z + u.z, v.w + u.w);
+      }
+      const uint32_t off = part_off(static_cast<int>(pbase) + r, H, D, h, d);
+      if (fold) {
+        const float4 pv = ld_dev4(rs, off);
+        const float x = mbuf[r], y = nbuf[r];
+        v = make_float4(x * v.x + y * pv.x, x * v.y + y * pv.y, x * v.z + y * pv.z,
+                        x * v.w + y * pv.w);
+      }
+      st_dev4(rs, off, v.x, v.y, v.z, v.w);
+    }
+  }
+  if (w == 0 && g == 0) {
+#pragma unroll
+    for (int t = 0; t < NRT; ++t) {
+      const int r = 16 * t + l16;
+      if (r < nrows) {
+        float* pml = reinterpret_cast<float*>(P.ws_ml + (pbase + r) * H + h);
+        st_dev(pml, Mrow[t]);
+        st_dev(pml + 1, Nrow[t]);
+      }
+    }
+  }
+  if (P.cnt) cf_arrive<OUT_T, D, R>(P, rb, nrows, h, reinterpret_cast<float (*)[R]>(mbuf), fl);
+}
+
 // Lazy reference maximum of the chunk-first softmax (log2 units): P <= 2^8.
 constexpr float kLazyMax = 8.f;
 
@@ -738,9 +856,6 @@ __device__ __forceinline__ void kcf_f16_block(const KcfParams& P, int seg, int z
   const int chain = __builtin_amdgcn_readfirstlane(w >> 2);  // chain (wave-uniform)
   const int l16 = lane & 15, g = lane >> 4;
   _Float16* vw = reinterpret_cast<_Float16*>(lds) + w * 16 * RS;
-  float* obuf = reinterpret_cast<float*>(lds);
-  float* mbuf = reinterpret_cast<float*>(lds + BIG);  // [NW][R]
-  float* nbuf = mbuf + NW * R;                        // [NW][R]
 
   // The segment's slots sit at a fixed stride, so they are requested with
   // the segment record, in the same round trip (one per lane).
@@ -968,286 +1083,230 @@ __device__ __forceinline__ void kcf_f16_block(const KcfParams& P, int seg, int z
     cur = nxt;
   }
 
-  finish_ids(P, fl);
-  // Merge the wavefront states per row: common max, rescaled sums.
+  cf_publish<OUT_T, D, NRT, NCH>(P, sg, rb, nrows, h, lds, BIG, m_run, n_part, fl,
+                                 [&](int t, float* row, float scale) {
 #pragma unroll
-  for (int t = 0; t < NRT; ++t) {
-    float ns = n_part[t];
-    ns += __shfl_xor(ns, 16);
-    ns += __shfl_xor(ns, 32);
-    if (g == 0) {
-      mbuf[w * R + 16 * t + l16] = m_run[t];
-      nbuf[w * R + 16 * t + l16] = ns;
-    }
-  }
-  __syncthreads();  // all wavefronts are past their loops: the slices are free
-  float scale[NRT], Mrow[NRT], Nrow[NRT];
-#pragma unroll
-  for (int t = 0; t < NRT; ++t) {
-    const int r = 16 * t + l16;
-    float M = kNegBig;
-#pragma unroll
-    for (int ww = 0; ww < NW; ++ww) M = fmaxf(M, mbuf[ww * R + r]);
-    float N = 0.f;
-#pragma unroll
-    for (int ww = 0; ww < NW; ++ww) N += nbuf[ww * R + r] * fast_exp2(mbuf[ww * R + r] - M);
-    scale[t] = fast_exp2(m_run[t] - M);
-    Mrow[t] = M;
-    Nrow[t] = N;
-  }
-  // every wavefront parks its rescaled O^T in its own buffer ([row][d], one
-  // 16-byte write per tile); the partial stores below add them up
-  {
-    float* mine = obuf + w * (R * OS);
-#pragma unroll
-    for (int t = 0; t < NRT; ++t) {
-      if (t < nrt) {
-        const int r = 16 * t + l16;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-          *reinterpret_cast<floatx4*>(mine + r * OS + 16 * dt + 4 * g) = acc[dt][t] * scale[t];
-      }
-    }
-  }
-  __syncthreads();
-  // write the segment's partial (O, m, n) for every covered row
-  const size_t pbase = static_cast<size_t>(sg.part_base + (rb - sg.row_begin));
-  const bool fold = sg.pad0 != 0;
-  if (fold) {
-    // serial reduction: fold into the row's accumulator (Eqn 2), which an
-    // earlier launch wrote; per-row factors go through mbuf / nbuf (free now)
-    if (w == 0 && g == 0) {
-#pragma unroll
-      for (int t = 0; t < NRT; ++t) {
-        const int r = 16 * t + l16;
-        if (r < nrows) {
-          const float* pml = reinterpret_cast<const float*>(P.ws_ml + (pbase + r) * H + h);
-          const float mp = ld_dev(pml), np = ld_dev(pml + 1);
-          const float mx = fmaxf(Mrow[t], mp);
-          const float x = fast_exp2(Mrow[t] - mx), y = fast_exp2(mp - mx);
-          mbuf[r] = x;
-          nbuf[r] = y;
-          Mrow[t] = mx;
-          Nrow[t] = x * Nrow[t] + y * np;
-        }
-      }
-    }
-    __syncthreads();
-  }
-  {
-    const __amdgpu_buffer_rsrc_t rs = part_rsrc(P.ws_o, P.o_bytes);
-    for (int e = tid; e < nrows * (D / 4); e += 256 * NCH) {
-      const int r = e / (D / 4), d = 4 * (e % (D / 4));
-      float4 v = *reinterpret_cast<const float4*>(obuf + r * OS + d);
-#pragma unroll
-      for (int ww = 1; ww < NW; ++ww) {
-        const float4 u = *reinterpret_cast<const float4*>(obuf + ww * (R * OS) + r * OS + d);
-        v = make_float4(v.x + u.x, v.y + u.y, v.z + u.z, v.w + u.w);
-      }
-      const uint32_t off = part_off(static_cast<int>(pbase) + r, H, D, h, d);
-      if (fold) {
-        const float4 pv = ld_dev4(rs, off);
-        const float x = mbuf[r], y = nbuf[r];
-        v = make_float4(x * v.x + y * pv.x, x * v.y + y * pv.y, x * v.z + y * pv.z,
-                        x * v.w + y * pv.w);
-      }
-      st_dev4(rs, off, v.x, v.y, v.z, v.w);
-    }
-  }
-  if (w == 0 && g == 0) {
-#pragma unroll
-    for (int t = 0; t < NRT; ++t) {
-      const int r = 16 * t + l16;
-      if (r < nrows) {
-        float* pml = reinterpret_cast<float*>(P.ws_ml + (pbase + r) * H + h);
-        st_dev(pml, Mrow[t]);
-        st_dev(pml + 1, Nrow[t]);
-      }
-    }
-  }
-  if (P.cnt) cf_arrive<OUT_T, D, R>(P, rb, nrows, h, reinterpret_cast<float (*)[R]>(mbuf), fl);
+                                   for (int dt = 0; dt < DT; ++dt)
+                                     *reinterpret_cast<floatx4*>(row + 16 * dt + 4 * g) =
+                                         acc[dt][t] * scale;
+                                 });
 }
 
-// fp32 chunk-first on the 16x16x4 fp32 matrix-core op (operands are single
-// floats: A row l16, k = g; B column l16, k = g), with the earlier schedule:
-// wavefront w computes S^T for tokens 16w..16w+15 of each 64-token block and
-// O^T for the d columns [w*D/4, (w+1)*D/4), so P = exp2(S - m) goes through
-// LDS ([row][token]) and V is staged in LDS ([token][d], rows padded by one
-// element), with barriers inside the chunk loop.
-template <int D, int NRT>
+// Chunk-first block, fp32, on the 16x16x4 fp32 matrix-core op (operands are
+// single floats: A row l16, k = g; B column l16, k = g). As in the fp16 block
+// wavefront w owns tokens 16w..16w+15 of every 64-token block and works on its
+// own, with no barrier and no LDS inside the chunk loop:
+//   S^T = K Q^T: a lane's 16-byte granule 16s + 4g .. + 3 of its K row and of
+//     its q row feeds four ops (op e contracts d = 16s + 4g + e over g);
+//   O^T += V^T P^T: the lane holds S^T, and so P^T, for tokens 4g + i of row
+//     l16, which is the B operand of the op that contracts tokens 4g + i over
+//     g; its A operand is element e of the lane's 16-byte granule
+//     64c + 4 l16 .. + 3 of V row 4g + i, so output tile (c, e) holds the
+//     columns 64c + 4 m + e (m = 0..15) of O.
+// V rows go from memory straight into the operand registers. The op runs at
+// 64 FLOP per cycle and SIMD: 64 ops of 32 cycles per 64-token block and
+// wavefront, a quarter of the block's time at the HBM rate; what bounds the
+// block is the latency of its K/V rows. Before, K rows came in 4-byte pieces
+// (16 rows apart), q was re-read in every step and P and V went through LDS
+// with three barriers a step: 32 rows over a 2048-token prompt with 256
+// private tokens each took 147 us, now 60 us (5.6 TB/s); 48 rows of d = 64
+// over 1,500 shared tokens 110 us, now 25 us.
+template <int D, int NRT, int NCH = 1>
 constexpr int kcf_f32_lds_bytes() {
-  return 64 * (D + 1) * 4 + 16 * NRT * (64 + 1) * 4 + 4 * 16 * NRT * 4;
+  return 4 * NCH * 16 * NRT * (D + 4) * 4 + 2 * 4 * NCH * 16 * NRT * 4;
 }
 
-template <int D, int NRT, typename OUT_T = float>
+template <int D, int NRT, typename OUT_T = float, int NCH = 1>
 __device__ __forceinline__ void kcf_f32_block(const KcfParams& P, int seg, int z, int h, char* lds) {
-  constexpr int DT = D / 64;
-  constexpr int VS = D + 1;
-  constexpr int PS = 64 + 1;
+  constexpr int KS = D / 16;      // 16-byte granules of a K row per lane
+  constexpr int VC = D / 64;      // 16-byte granules of a V row per lane
   constexpr int R = 16 * NRT;
-  float* v_lds = reinterpret_cast<float*>(lds);
-  float* p_lds = v_lds + 64 * VS;
-  auto red = reinterpret_cast<float (*)[R]>(p_lds + R * PS);
+  constexpr int BIG = 4 * NCH * R * (D + 4) * 4;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int wq = w & 3;                                       // token quarter of a block
+  const int chain = __builtin_amdgcn_readfirstlane(w >> 2);  // chain (wave-uniform)
+  const int l16 = lane & 15, g = lane >> 4;
 
   const CfSeg sg = P.segs[seg];
+  const int my_slot = P.seg_slots[(P.seg_base + seg) * kSegSlotStride + lane];
   const int H = P.H, C = P.C;
   const int rb = sg.row_begin + z * R;
   const int nrows = min(R, sg.row_end - rb);
   if (nrows <= 0) return;
   FinishList fl;
-  finish_range<R>(P, rb, nrows, fl);
   const int nrt = (nrows + 15) / 16;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int l16 = lane & 15, g = lane >> 4;
   const float* q = static_cast<const float*>(P.q);
-  const float* kpool = static_cast<const float*>(P.kpool);
-  const float* vpool = static_cast<const float*>(P.vpool);
+  const float* kpool = static_cast<const float*>(P.kpool) + h * P.hs;
+  const float* vpool = static_cast<const float*>(P.vpool) + h * P.hs;
+  const size_t slot_stride = static_cast<size_t>(P.ss);
 
+  // q rows (a lane past the covered rows reads a covered row, keeps zeros)
+  floatx4 qf[NRT][KS];
+#pragma unroll
+  for (int t = 0; t < NRT; ++t) {
+    const int r = 16 * t + l16;
+    const float* qp = q + (static_cast<size_t>(io_row(P.row_map, rb + min(r, nrows - 1))) * H + h) * D + 4 * g;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const floatx4 x = *reinterpret_cast<const floatx4*>(qp + 16 * s);
+      qf[t][s] = r < nrows ? x : floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
   float m_run[NRT], n_part[NRT];
-  floatx4 acc[DT][NRT];
+  floatx4 acc[VC][4][NRT];
 #pragma unroll
   for (int t = 0; t < NRT; ++t) {
     m_run[t] = kNegBig;
     n_part[t] = 0.f;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) acc[dt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < VC; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[c][e][t] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
 
-  for (int ci = 0; ci < sg.n_chunks; ++ci) {
-    const int slot = P.seg_slots[sg.slot_off + ci];
-    const int len = P.slot_len[slot];
-    const size_t base = static_cast<size_t>(slot) * P.ss + h * P.hs;
-    const float* kb = kpool + base;
-    const float* vb = vpool + base;
-    for (int t0 = 0; t0 < len; t0 += 64) {
-      const int nt = min(64, len - t0);
-      constexpr int PIECES = 64 * D / 4;
-      for (int pc = tid; pc < PIECES; pc += 256) {
-        const int tok = pc / (D / 4), col = (pc % (D / 4)) * 4;
-        float4 val = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (tok < nt) val = *reinterpret_cast<const float4*>(vb + static_cast<size_t>(t0 + tok) * D + col);
-        float* dst = v_lds + tok * VS + col;
-        dst[0] = val.x;
-        dst[1] = val.y;
-        dst[2] = val.z;
-        dst[3] = val.w;
+  const int my_len = lane < sg.n_chunks ? P.slot_len[my_slot] : 0;
+  const int nch = sg.n_chunks;
+  const int ko = ((16 * wq + l16) * D + 4 * g) * 4;      // this lane's K granule s = 0, bytes
+  const int vo = ((16 * wq + 4 * g) * D + 4 * l16) * 4;  // V granule of token 4g, c = 0
+  floatx4 kf[KS], vf[4][VC];
+  // rows t0 .. of the chunk in `slot` through a descriptor over its valid
+  // rows (rows past the length read as zeros)
+  auto rows_rsrc = [&](const float* pool, int slot, int t0, int len) {
+    const int sl = __builtin_amdgcn_readfirstlane(slot);
+    const int t = __builtin_amdgcn_readfirstlane(t0);
+    const int ntb = min(64, __builtin_amdgcn_readfirstlane(len) - t);
+    return __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(pool + sl * slot_stride + static_cast<size_t>(t) * D), 0, ntb * D * 4, kRsrcWord3);
+  };
+  auto load_k = [&](int slot, int t0, int len) {
+    const __amdgpu_buffer_rsrc_t r = rows_rsrc(kpool, slot, t0, len);
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      kf[s] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, ko + 64 * s, 0, 0));
+  };
+  auto load_v = [&](int slot, int t0, int len) {
+    const __amdgpu_buffer_rsrc_t r = rows_rsrc(vpool, slot, t0, len);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int c = 0; c < VC; ++c)
+        vf[i][c] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, vo + (i * D + 64 * c) * 4, 0, 0));
+  };
+
+  // The first block's rows go out before the chunk's length is known, as if
+  // it were full (in bounds; a shorter chunk is requested again).
+  const int cm = min(C, 64);
+  int j = chain, t0 = 0, slot = __builtin_amdgcn_readlane(my_slot, chain), len = cm;
+  const bool work = chain < nch;
+  if (work) {
+    load_k(slot, 0, cm);
+    load_v(slot, 0, cm);
+  }
+  finish_range<R>(P, rb, nrows, fl);
+  len = __builtin_amdgcn_readlane(my_len, chain);
+  if (work && len < cm) {  // uniform; rare
+    load_k(slot, 0, len);
+    load_v(slot, 0, len);
+  }
+  while (work) {
+    // the next block: its K rows are requested as soon as this block's have
+    // been used, its V rows likewise; past the end the last block's again
+    int jn = j, tn = t0 + 64, sn = slot, ln = len;
+    if (tn >= len) {
+      tn = 0;
+      jn += NCH;
+      if (jn < nch) {
+        sn = __builtin_amdgcn_readlane(my_slot, jn);
+        ln = __builtin_amdgcn_readlane(my_len, jn);
       }
-      const int ktok = 16 * w + l16;
-      floatx4 sacc[NRT];
-#pragma unroll
-      for (int t = 0; t < NRT; ++t) sacc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-      for (int s = 0; s < D / 4; ++s) {
-        const float a = ktok < nt ? kb[static_cast<size_t>(t0 + ktok) * D + 4 * s + g] : 0.f;
-#pragma unroll
-        for (int t = 0; t < NRT; ++t) {
-          if (t < nrt) {
-            const int r = 16 * t + l16;
-            const float b = r < nrows ? q[(static_cast<size_t>(io_row(P.row_map, rb + r)) * H + h) * D + 4 * s + g] : 0.f;
-            sacc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, sacc[t], 0, 0, 0);
-          }
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < NRT; ++t) {
-        float lmax = kNegBig;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int tok = 16 * w + 4 * g + i;
-          const float x = tok < nt ? sacc[t][i] * P.qscale : -INFINITY;
-          sacc[t][i] = x;
-          lmax = fmaxf(lmax, x);
-        }
-        lmax = fmaxf(lmax, __shfl_xor(lmax, 16));
-        lmax = fmaxf(lmax, __shfl_xor(lmax, 32));
-        if (g == 0) red[w][16 * t + l16] = lmax;
-      }
-      __syncthreads();
-      float alpha[NRT];
-#pragma unroll
-      for (int t = 0; t < NRT; ++t) {
-        const int r = 16 * t + l16;
-        const float bmax = fmaxf(fmaxf(red[0][r], red[1][r]), fmaxf(red[2][r], red[3][r]));
-        const float mn = fmaxf(m_run[t], bmax);
-        alpha[t] = fast_exp2(m_run[t] - mn);
-        m_run[t] = mn;
-        float ps = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float p = fast_exp2(sacc[t][i] - mn);
-          ps += p;
-          p_lds[r * PS + 16 * w + 4 * g + i] = p;
-        }
-        n_part[t] = n_part[t] * alpha[t] + ps;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        const int d0 = w * (D / 4) + 16 * dt;
-#pragma unroll
-        for (int t = 0; t < NRT; ++t) acc[dt][t] *= alpha[t];
-        for (int ks = 0; ks < 16; ++ks) {
-          const float va = v_lds[(4 * ks + g) * VS + d0 + l16];
-#pragma unroll
-          for (int t = 0; t < NRT; ++t) {
-            if (t < nrt) {
-              const float pb = p_lds[(16 * t + l16) * PS + 4 * ks + g];
-              acc[dt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(va, pb, acc[dt][t], 0, 0, 0);
-            }
-          }
-        }
-      }
-      __syncthreads();
     }
+    const bool more = jn < nch;
+    if (!more) {
+      tn = len - 1;  // one row
+      sn = slot;
+      ln = len;
+    }
+    const int nt = min(64, len - t0);
+    floatx4 sacc[NRT];
+#pragma unroll
+    for (int t = 0; t < NRT; ++t) {
+      // two chains of dependent ops instead of one
+      floatx4 s0 = floatx4{0.f, 0.f, 0.f, 0.f}, s1 = floatx4{0.f, 0.f, 0.f, 0.f};
+      if (t < nrt) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+          for (int e = 0; e < 4; e += 2) {
+            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[s][e], qf[t][s][e], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[s][e + 1], qf[t][s][e + 1], s1, 0, 0, 0);
+          }
+      }
+      sacc[t] = s0 + s1;
+    }
+    load_k(sn, tn, ln);
+    // online softmax with a lazy reference maximum, as in the fp16 block
+    floatx4 p[NRT];
+    float alpha[NRT];
+    bool moved = false;
+#pragma unroll
+    for (int t = 0; t < NRT; ++t) {
+      float lmax = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int tok = 16 * wq + 4 * g + i;
+        const float x = tok < nt ? sacc[t][i] * P.qscale : -INFINITY;
+        sacc[t][i] = x;
+        lmax = fmaxf(lmax, x);
+      }
+      lmax = rows4_max(lmax);
+      const float mn = lmax > m_run[t] + kLazyMax ? lmax : m_run[t];
+      alpha[t] = fast_exp2(m_run[t] - mn);
+      moved |= mn != m_run[t];
+      m_run[t] = mn;
+      float ps = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        p[t][i] = fast_exp2(sacc[t][i] - mn);
+        ps += p[t][i];
+      }
+      n_part[t] = n_part[t] * alpha[t] + ps;
+    }
+    if (__any(moved)) {
+#pragma unroll
+      for (int t = 0; t < NRT; ++t)
+#pragma unroll
+        for (int c = 0; c < VC; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[c][e][t] *= alpha[t];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int c = 0; c < VC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < NRT; ++t)
+            if (t < nrt)
+              acc[c][e][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][c][e], p[t][i], acc[c][e][t], 0, 0, 0);
+    load_v(sn, tn, ln);
+    if (!more) break;
+    j = jn;
+    t0 = tn;
+    slot = sn;
+    len = ln;
   }
 
-  finish_ids(P, fl);
+  cf_publish<OUT_T, D, NRT, NCH>(P, sg, rb, nrows, h, lds, BIG, m_run, n_part, fl,
+                                 [&](int t, float* row, float scale) {
 #pragma unroll
-  for (int t = 0; t < NRT; ++t) {
-    float ns = n_part[t];
-    ns += __shfl_xor(ns, 16);
-    ns += __shfl_xor(ns, 32);
-    if (g == 0) red[w][16 * t + l16] = ns;
-  }
-  __syncthreads();
-  // m_run is the same in every wavefront (block-wide maxima), so each lane
-  // derives its row's fold factors itself
-  const bool fold = sg.pad0 != 0;
+                                   for (int c = 0; c < VC; ++c)
 #pragma unroll
-  for (int t = 0; t < NRT; ++t) {
-    const int r = 16 * t + l16;
-    if (r < nrows) {
-      const size_t p = static_cast<size_t>(sg.part_base + (rb - sg.row_begin) + r);
-      const __amdgpu_buffer_rsrc_t rs = part_rsrc(P.ws_o, P.o_bytes);
-      float* pml = reinterpret_cast<float*>(P.ws_ml + p * H + h);
-      float m = m_run[t], n = red[0][r] + red[1][r] + red[2][r] + red[3][r];
-      float x = 1.f, y = 0.f;
-      if (fold) {
-        // serial reduction: fold into the row's accumulator (Eqn 2)
-        const float mp = ld_dev(pml), np = ld_dev(pml + 1);
-        const float mx = fmaxf(m, mp);
-        x = fast_exp2(m - mx);
-        y = fast_exp2(mp - mx);
-        m = mx;
-        n = x * n + y * np;
-      }
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        floatx4 v = acc[dt][t];
-        const uint32_t off = part_off(static_cast<int>(p), H, D, h, w * (D / 4) + 16 * dt + 4 * g);
-        if (fold) {
-          const float4 pv = ld_dev4(rs, off);
-          v = floatx4{x * v[0] + y * pv.x, x * v[1] + y * pv.y, x * v[2] + y * pv.z,
-                      x * v[3] + y * pv.w};
-        }
-        st_dev4(rs, off, v[0], v[1], v[2], v[3]);
-      }
-      if (w == 0 && g == 0) {
-        st_dev(pml, m);
-        st_dev(pml + 1, n);
-      }
-    }
-  }
-  if (P.cnt) cf_arrive<OUT_T, D, R>(P, rb, nrows, h, red, fl);
+                                     for (int i = 0; i < 4; ++i)
+                                       *reinterpret_cast<floatx4*>(row + 64 * c + 16 * g + 4 * i) =
+                                           floatx4{acc[c][0][t][i], acc[c][1][t][i], acc[c][2][t][i],
+                                                   acc[c][3][t][i]} * scale;
+                                 });
 }
 
 // ---------------------------------------------------------------------------
@@ -1316,8 +1375,17 @@ constexpr int tpp_lds_bytes() {
   return cf > sf ? cf : sf;
 }
 
+// Resident blocks per compute unit. The fp32 chunk-first path at d = 128
+// holds 32 registers each of K, V, q and O^T; capped at 128 for four blocks it
+// spills 63 of them. Three blocks still have twice the fp16 block's bytes in
+// flight each.
+template <typename T, int D>
+constexpr int tpp_blocks_per_cu() {
+  return sizeof(T) == 4 && D == 128 ? 3 : 4;
+}
+
 template <typename T, int D, int NRT>
-__global__ __launch_bounds__(256, 4) void tpp_kernel(TppParams P) {
+__global__ __launch_bounds__(256, (tpp_blocks_per_cu<T, D>())) void tpp_kernel(TppParams P) {
   __shared__ __attribute__((aligned(16))) char lds[tpp_lds_bytes<T, D, NRT>()];
   const int b = static_cast<int>(blockIdx.x);
   const int H = P.sf.H;
@@ -1353,17 +1421,23 @@ __global__ __launch_bounds__(256) void kcf_kernel(KcfParams P, int zb) {
 // Chunk-first work alone (no sequence-first item in the call, e.g. identical
 // sequences): 16-row blocks of eight wavefronts, two chains of four that take
 // alternate chunks of the segment, so each block keeps twice the loads in
-// flight and the chains' states are merged once at the end. Measured on
+// flight and the chains' states are merged once at the end (fp32: 32
+// identical sequences of 4,096 tokens 223 us in the one-chain launch of the
+// earlier fp32 block, 37.5 us so). Measured on
 // Table 3's all-shared cells against one chain with a two-deep prefetch
 // (same) and four chains (slower: more fixed cost per chain).
 constexpr int kDeepChains = 2;
-template <int D>
+template <typename T, int D>
 __global__ __launch_bounds__(256 * kDeepChains) void kcf_deep_kernel(KcfParams P, int zb) {
-  __shared__ __attribute__((aligned(16))) char lds[kcf_f16_lds_bytes<D, 1, kDeepChains>()];
+  constexpr int L = sizeof(T) == 2 ? kcf_f16_lds_bytes<D, 1, kDeepChains>() : kcf_f32_lds_bytes<D, 1, kDeepChains>();
+  __shared__ __attribute__((aligned(16))) char lds[L];
   const int b = static_cast<int>(blockIdx.x);
   const int h = b % P.H;
   const int rest = b / P.H;
-  kcf_f16_block<D, 1, _Float16, kDeepChains>(P, rest / zb, rest % zb, h, lds);
+  if constexpr (sizeof(T) == 2)
+    kcf_f16_block<D, 1, _Float16, kDeepChains>(P, rest / zb, rest % zb, h, lds);
+  else
+    kcf_f32_block<D, 1, float, kDeepChains>(P, rest / zb, rest % zb, h, lds);
 }
 
 template <typename T, int D>
@@ -1380,11 +1454,9 @@ hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, h
   if ((schedule == 1 || schedule == 2) && both) {
     // the fused launch always takes 16-row chunk-first blocks
     if constexpr (NRT == 1) {
-      if constexpr (sizeof(T) == 2) {
-        if (n_sf == 0) {  // chunk-first work alone
-          if (P.n_cf > 0) kcf_deep_kernel<D><<<P.n_cf, 256 * kDeepChains, 0, s>>>(P.cf, P.zb);
-          return hipSuccess;
-        }
+      if (n_sf == 0) {  // chunk-first work alone
+        if (P.n_cf > 0) kcf_deep_kernel<T, D><<<P.n_cf, 256 * kDeepChains, 0, s>>>(P.cf, P.zb);
+        return hipSuccess;
       }
       const int grid = P.n_cf + n_sf;
       if (grid > 0) tpp_kernel<T, D, NRT><<<grid, 256, 0, s>>>(P);

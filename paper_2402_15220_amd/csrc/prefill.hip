@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64 * WPG * NGRP) void kpf_kernel(KpfParams P,
     // from a vector register then costs a per-lane loop around every load
     const int m = min(TOK, chunk_end(j) - chunk_start(j) - r0);
     int rows;
-    asm("s_max_i32 %0, %1, 0" : "=s"(rows) : "s"(m));
+    asm("s_max_i32 %0, %1, 0" : "=s"(rows) : "s"(m) : "scc");
     const size_t base = static_cast<size_t>(slot) * slot_stride + static_cast<size_t>(r0) * D;
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<_Float16*>(kbase + base), 0, rows * D * 2, kRsrcWord3);

@@ -822,6 +822,7 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
   }
   a.n_chunks = nc;
   a.n_q = static_cast<int>(n_q);
+  a.L = pos;
   const float sc = scale == 0.f ? 1.f / std::sqrt(static_cast<float>(a.D)) : scale;
   a.qscale = sc * 1.4426950408889634f;
   // Key-range split: when the (64-query tile, head) blocks alone would leave
@@ -838,6 +839,20 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
   else if (tiles < cache->num_cus)
     split = std::min<int64_t>({(cache->num_cus + tiles - 1) / tiles, std::max<int64_t>(1, units / 6), 16});
   a.n_split = static_cast<int>(split);
+  // 32-query wavefronts wherever their tiles give every compute unit a block:
+  // 128-query tiles (each K/V element through the caches once per 128
+  // queries), else 64-query ones, which also move small chunks in 32-row
+  // units instead of 64; smaller joins are latency-bound and keep the 16-query
+  // blocks and their key-range split. 32 heads, 16-query / 64 / 128-query
+  // blocks: 1,100 queries over 1,100 positions 38.2 / 25.9 / 27.2 us, 900 over
+  // 1,200 38.2 / 27.9 / 27.1, 512 over 1,536 24.9 / 24.8 / 31.0, the same in
+  // 16-token chunks 61.1 / 34.8 / -, 300 over 300 9.3 / 9.7 / 10.6, 200 over
+  // 1,224 16.9 / 20.4 / 25.4. At d = 64 a 64-query tile has too little work per
+  // unit: 16 heads, 1,024 over 2,024 20.0 / 21.8 us.
+  if (split == 1) {
+    if ((n_q + 127) / 128 * a.H >= cache->num_cus) a.tile_rows = 128;
+    else if (tiles >= cache->num_cus && (a.D == 128 || a.C <= 32)) a.tile_rows = 64;
+  }
   if (split > 1) {
     const size_t ws = static_cast<size_t>(tiles * split) * ca::prefill_part_bytes(a.D);
     if ((st = ensure_device(reinterpret_cast<char**>(&cache->d_pf_ws), &cache->d_pf_ws_cap, ws, s,

@@ -79,12 +79,16 @@ struct PrefillArgs {
   const int32_t* chunk_start;  // device [n_chunks + 1]
   int n_chunks;
   int n_q;
+  int L;         // positions of the path
   float qscale;  // softmax scale * log2(e)
   // Key-range split of each (64-query tile, head): n_split parts in separate
   // blocks; for n_split > 1, ws holds tiles * n_split partials of
   // prefill_part_bytes(D) each and cnt one zeroed counter per tile
   // (tiles = ceil(n_q / 64) * H); the kernel leaves the counters at zero.
   int n_split = 1;
+  // Queries per tile of 32-query wavefronts, one block per (tile, head): 128
+  // or 64 (n_split must be 1); 0: the 16-query wavefronts' 64-query tiles.
+  int tile_rows = 0;
   float* ws = nullptr;
   size_t ws_bytes = 0;  // bytes of ws the launch may touch (below 4 GiB)
   int32_t* cnt = nullptr;

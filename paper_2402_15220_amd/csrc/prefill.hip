@@ -5,6 +5,7 @@
 
 #include <cfloat>
 #include <cstdint>
+#include <type_traits>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -64,6 +65,7 @@ struct KpfParams {
   int32_t* cnt;                 // n_split > 1: arrival counter per tile, zero between launches
   int cnt_shift;                // counter of tile t is cnt[t << cnt_shift] (tile_counter_shift)
   uint32_t ws_bytes;            // bytes of ws (below 4 GiB: 32-bit buffer offsets)
+  int L;                        // positions of the path
 };
 
 // floats of one partial: unnormalised O of 64 query rows, their maxima and sums
@@ -571,6 +573,465 @@ __global__ __launch_bounds__(64 * WPG * NGRP) void kpf_kernel(KpfParams P,
   }
 }
 
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+
+// Large joins: tiles of 32 * QW queries, QW wavefronts per key group, KG
+// groups that take alternate units, and the same online softmax as above, on
+// the 32x32x16 op (a wavefront owns 32 queries, so each K or V fragment read
+// from LDS feeds twice the arithmetic of the 16-query block):
+//   S^T = K Q^T: lane (l32, hl) holds S^T[token 8b + 4 hl + i][query l32] of a
+//     32-token tile in register 4b + i, so the row maximum needs one exchange
+//     between the two halves of the wavefront;
+//   O^T += V^T P^T: P^T as the B operand in the registers S^T came out in, the
+//     V^T fragments through ds_read_b64_tr_b16.
+// What bounds it: a 64-token unit costs a wavefront 32 matrix ops of 32 cycles
+// and, on the same issue port, ~130 vector ops (32 of them exponentials of 8.5
+// cycles); a wavefront alone issues an instruction every ~5 cycles, so with two
+// wavefronts per SIMD the number of instructions matters as much as either
+// pipe. Hence:
+//   - rows go from memory straight into LDS (no registers, no LDS writes);
+//   - the scores of unit i + 1 are issued between the exponentials of unit i,
+//     the O update of unit i between the row maxima of unit i + 1, in a fixed
+//     order;
+//   - every LDS address is a per-lane register plus an immediate (the tile of
+//     a step is a constant of the unrolled loop), and a unit's descriptor is
+//     four v_readlane from a 64-chunk window held one chunk per lane;
+//   - masks use min with +-inf rather than 32 lane masks, which spilled the
+//     scalar registers.
+// Measured against the 16-query block: 2,048 queries over 8,192 positions 412
+// -> 270 us (890 TFLOP/s), 4,096 over 4,096 262 -> 175, 1,100 over 1,100 38.2
+// -> 27.2, and with 64-query tiles 2,100 over 5,100 (8 heads) 104 -> 67 and
+// 512 over 1,536 unchanged (there every block streams the whole path and the
+// 200 MB through the L2s set ~20 us).
+// Tried, no faster: 256-query tiles (long prefixes 5% faster, others slower),
+// three or four LDS tiles, K/V staged through registers, offsetting one half
+// of the wavefronts by half a step.
+template <int D, int QW, int KG, int TOK, int NI>
+__global__ __launch_bounds__(64 * QW * KG, 2) void kpw_kernel(KpfParams P, const int32_t* __restrict__ cslot,
+                                                              const int32_t* __restrict__ cstart,
+                                                              const KpfPath<(NI > 0 ? NI : 1)> path) {
+  constexpr int QR = 32 * QW;       // query rows of a tile
+  constexpr int KS = D / 16;        // 32x32x16 steps over d
+  constexpr int DT = D / 32;        // 32-wide d tiles of O^T
+  constexpr int NG = D / 8;         // 16-byte granules per token row
+  constexpr int JT = TOK / 32;      // 32-token tiles of S^T per unit
+  constexpr int RPI = 512 / D;      // token rows a wavefront's load moves (64 x 16 bytes)
+  constexpr int LPT = TOK / RPI / QW;  // loads per wavefront and tile
+  constexpr int TB = TOK * D * 2;   // LDS bytes of a K or V tile
+  constexpr int GB = 4 * TB;        // of a group: two tiles of K, two of V
+  constexpr int OST = D + 4;        // merge buffer row stride (floats)
+  static_assert(TOK == 32 * JT && LPT * RPI * QW == TOK, "unit shape");
+  static_assert(2 * GB * KG <= 160 * 1024, "two blocks per compute unit");
+  constexpr int MB = (KG - 1) * QR * (OST + 2) * 4;  // merge buffer, in the tiles' place
+  static_assert(MB <= 80 * 1024, "merge buffer");
+  __shared__ __attribute__((aligned(1024))) char lds[GB * KG > MB ? GB * KG : MB];
+  auto chunk_slot = [&](int j) -> int {
+    if constexpr (NI > 0) return path.slot[j];
+    else return cslot[j];
+  };
+  auto chunk_start = [&](int j) -> int {  // j up to n_chunks
+    if constexpr (NI > 0) return path.start[j];
+    else return cstart[j];
+  };
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave / QW, w = wave % QW;
+  const int l32 = lane & 31, hl = lane >> 5;
+  // LDS byte of the group's K and V tile b
+  auto tile_k = [&](int b) { return grp * GB + b * TB; };
+  auto tile_v = [&](int b) { return grp * GB + (2 + b) * TB; };
+  const int H = P.H, n_q = P.n_q;
+  const int n_qt = (n_q + QR - 1) / QR;
+  const int per_xcd = static_cast<int>(gridDim.x) / 8;
+  const int v = static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
+  if (v >= n_qt * H) return;
+  const int h = v / n_qt;
+  const int q0 = (n_qt - 1 - v % n_qt) * QR;  // the longest tiles of a head first
+  const int qi = q0 + 32 * w + l32;
+  half8 qf[KS];
+  {
+    const int qr = min(qi, n_q - 1);
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      qf[s] = *reinterpret_cast<const half8*>(P.q + (static_cast<size_t>(qr) * H + h) * D + 16 * s + 8 * hl);
+  }
+  const int L = P.L;
+  const int pos_last = L - n_q + min(q0 + QR - 1, n_q - 1);
+  const int pos_first = L - n_q + q0 + 32 * w;  // first position of the wavefront's queries
+  const int pos = L - n_q + qi;
+  const _Float16* kbase = P.kpool + h * P.hs;
+  const _Float16* vbase = P.vpool + h * P.hs;
+  const int upc = (P.C + TOK - 1) / TOK;
+
+  float m_run = kNegBig, n_run = 0.f;
+  floatx16 acc[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
+
+  // A window of 64 chunks of the path, one per lane: offset of the chunk's
+  // rows in a head's pool (elements), first position and end. A unit's
+  // descriptor is read from it with v_readlane (no memory wait in the loop).
+  const int nc = P.n_chunks;
+  int win = 0, w_start = 0, w_end = 0;
+  int64_t w_off = 0;
+  auto load_window = [&](int wi) {
+    win = wi;
+    const int j = 64 * wi + lane;
+    const bool in = j < nc;
+    w_off = static_cast<int64_t>(chunk_slot(in ? j : 0)) * P.ss;
+    w_start = in ? chunk_start(j) : 0x7fffffff;
+    w_end = in ? chunk_start(j + 1) : 0x7fffffff;
+    // wait here, not where the loop reads them (that wait would also cover
+    // the rows requested for later steps)
+    asm volatile("" : "+v"(w_start), "+v"(w_end), "+v"(w_off));
+  };
+  load_window(0);
+  // chunks the tile needs, and those the wavefront's queries can see: a
+  // prefix of the path each (starts ascend)
+  int n_ch = 0, n_vis = 0;
+  for (int wi = 0;;) {
+    n_ch += __popcll(__ballot(w_start <= pos_last));
+    n_vis += __popcll(__ballot(w_start <= pos_first + 31));
+    if (n_ch < 64 * ++wi || 64 * wi >= nc) break;
+    load_window(wi);
+  }
+  const int n_units = n_ch * upc;  // at least one
+  const int steps = (n_units + KG - 1) / KG;
+  // steps of this group whose unit the wavefront sees something of (may be <= 0)
+  const int n_see = (n_vis * upc - grp + KG - 1) / KG;
+
+  struct Unit {
+    int64_t off;   // first row in a head's pool (elements)
+    int pos, len;  // first position, rows (<= 0: past a short chunk's end)
+  };
+  // descriptors of the group's units in order; past the end the last one again
+  int fu = min(grp, n_units - 1);
+  int fj = upc == 1 ? fu : fu / upc, fr = upc == 1 ? 0 : fu - fj * upc;
+  auto fetch = [&]() {  // after turn_window(); no branches
+    Unit d;
+    const int l = fj & 63;
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(w_off), l);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(w_off >> 32), l);
+    d.off = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo) + fr * (TOK * D);
+    d.pos = __builtin_amdgcn_readlane(w_start, l) + fr * TOK;
+    d.len = min(TOK, __builtin_amdgcn_readlane(w_end, l) - d.pos);
+    const bool more = fu + KG < n_units;
+    fu += more ? KG : 0;
+    fr += more ? KG : 0;
+#pragma unroll
+    for (int k = 0; k < KG; ++k) {
+      const bool c = fr >= upc;
+      fr -= c ? upc : 0;
+      fj += c ? 1 : 0;
+    }
+    return d;
+  };
+  auto turn_window = [&]() {
+    if ((fj >> 6) != win) load_window(fj >> 6);
+  };
+  // Rows go from memory straight into LDS (a wavefront's load writes 64
+  // consecutive 16-byte granules), so rows are not padded; instead granule c
+  // of row r sits at place c ^ swz(r) of its row, which keeps both the reads
+  // of one column of 32 rows (K) and of 64 bytes of four rows (V, transposing)
+  // free of bank conflicts.
+  auto swz = [](int r) {
+    return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+  };
+  // LDS byte address of lds[0]
+  const int lds0 = static_cast<int>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lds));
+  const int row0 = w * RPI + lane / NG;  // this lane's row in the wavefront's first load
+  constexpr int NGO = QW >= 4 ? 1 : 4 / QW;  // loads of different swizzle
+  int goff[NGO];
+#pragma unroll
+  for (int n = 0; n < NGO; ++n) {
+    const int r = row0 + n * QW * RPI;
+    goff[n] = row0 * (D * 2) + (((lane % NG) ^ swz(r)) * 16);
+  }
+  auto issue = [&](const _Float16* pool, int tile, const Unit& d) {
+    int rows;
+    asm("s_max_i32 %0, %1, 0" : "=s"(rows) : "s"(d.len) : "scc");
+    const uint64_t p = reinterpret_cast<uint64_t>(pool + d.off);
+    const u32x4 rs = {static_cast<uint32_t>(p), static_cast<uint32_t>(p >> 32) & 0xffffu,
+                      static_cast<uint32_t>(rows * D * 2), static_cast<uint32_t>(kRsrcWord3)};
+#pragma unroll
+    for (int n = 0; n < LPT; ++n)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                   :
+                   : "s"(lds0 + tile + (w + QW * n) * 1024), "v"(goff[n % NGO]), "s"(rs), "s"(n * QW * 1024)
+                   : "m0", "memory");
+  };
+  auto issue_k = [&](const Unit& d, int b) { issue(kbase, tile_k(b), d); };
+  auto issue_v = [&](const Unit& d, int b) { issue(vbase, tile_v(b), d); };
+  // read addresses: K granule 2s + hl of row l32 (+ 32 jt); V: lane i of a
+  // 16-lane group names 8 bytes of row 16p + 8e + 4 hl + i / 4, column
+  // 32 dt + 16 sub + 4 (i % 4)
+  int k_rd[KS], v_rd[DT][2];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) k_rd[s] = l32 * (D * 2) + (((2 * s + hl) ^ swz(l32)) * 16);
+  {
+    const int i16 = lane & 15, sub = (lane >> 4) & 1;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int r = 8 * e + 4 * hl + (i16 >> 2);
+        v_rd[dt][e] = r * (D * 2) + (((4 * dt + 2 * sub + ((i16 & 3) >> 1)) ^ swz(r)) * 16) + 8 * (i16 & 1);
+      }
+  }
+  auto read_k = [&](int b, int jt, int s) {
+    return *reinterpret_cast<const half8*>(lds + tile_k(b) + k_rd[s] + 32 * jt * (D * 2));
+  };
+  auto read_v = [&](int b, int p, int dt) {
+    const half4 v0 = lds_read_tr16(reinterpret_cast<const _Float16*>(lds + tile_v(b) + v_rd[dt][0] + 16 * p * (D * 2)));
+    const half4 v1 = lds_read_tr16(reinterpret_cast<const _Float16*>(lds + tile_v(b) + v_rd[dt][1] + 16 * p * (D * 2)));
+    return __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  auto scores = [&](floatx16 (&sa)[JT], int b) {
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sa[jt][i] = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        sa[jt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(read_k(b, jt, s), qf[s], sa[jt], 0, 0, 0);
+      }
+  };
+  half8 pb[2 * JT];
+  float n2 = 0.f;    // second accumulator of the row's sum
+  float lmax = 0.f;  // this half-wavefront's maximum of the unit in `cur`
+  auto rowmax = [&](const floatx16 (&sa)[JT]) {
+    float c[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};  // four short chains
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) c[r & 3] = fmaxf(c[r & 3], sa[jt][r]);
+    lmax = fmaxf(fmaxf(c[0], c[1]), fmaxf(c[2], c[3]));
+  };
+  // -inf where the unit's tokens are past its rows or after the query; done
+  // only for units that have such tokens (uniform), with their maximum again
+  auto mask = [&](floatx16 (&sa)[JT], const Unit& d) {
+    if (d.len >= TOK && d.pos + TOK - 1 <= pos_first) return;
+    // min with +inf for a visible token, -inf for another: three vector ops
+    // per element and no lane masks (32 of them spill the scalar registers)
+    const int last = min(d.len - 1, pos - d.pos) - 4 * hl;  // last visible token of the unit
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int x = last - (32 * jt + 8 * (r >> 2) + (r & 3));
+        sa[jt][r] = fminf(sa[jt][r], __int_as_float((x & INT32_MIN) | 0x7f800000));
+      }
+    rowmax(sa);
+  };
+  auto refmax = [&]() {
+    float a = lmax, c = lmax;
+    swap_halves32(a, c);
+    const float lm = fmaxf(a, c) * P.qscale;
+    const float mn = lm > m_run + kPfLazyMax ? lm : m_run;
+    const bool moved = mn != m_run;
+    if (__any(moved)) {
+      const float alpha = fast_exp2(m_run - mn);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) acc[dt] *= alpha;
+      n_run *= alpha;
+      n2 *= alpha;
+    }
+    m_run = mn;
+  };
+  // The loop's matrix ops, one at a time with the vector, LDS and memory
+  // work that goes between them; nothing but scalar work moves across the
+  // fences, so the order below is the order of issue.
+  constexpr int NS = KS * JT, NO = 2 * JT * DT;  // ops of the scores, of the O update
+  auto fence = []() { __builtin_amdgcn_sched_barrier(0x4); };
+  half8 va[DT];  // V^T fragments of the next ops
+  auto load_va = [&](int b, int k) { va[k % DT] = read_v(b, k / DT, k % DT); };
+  // P and row sums of elements e and e + 1 of the unit in sa
+  auto prob2 = [&](const floatx16 (&sa)[JT], int e) {
+    float2_t y;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      y[k] = fast_exp2(__builtin_fmaf(sa[(e + k) / 16][(e + k) % 16], P.qscale, -m_run));
+    const half2_t x = __builtin_convertvector(y, half2_t);
+    pb[e / 8][e % 8] = x[0];
+    pb[e / 8][e % 8 + 1] = x[1];
+    float& n = e & 2 ? n2 : n_run;
+    n = __builtin_amdgcn_fdot2(x, half2_t{1, 1}, n, false);
+  };
+  constexpr int EPO = 16 * JT / NS > 0 ? 16 * JT / NS : 1;  // elements of P per op of the scores
+  static_assert(EPO % 2 == 0 && EPO * NS == 16 * JT, "P elements per op");
+  // scores of the next unit against K tile bk, P of `cur`, first V^T fragments
+  auto scores_probs = [&](const floatx16 (&cur)[JT], floatx16 (&nxt)[JT], int bk, int bv) {
+    constexpr int RING = 4;
+    half8 ka[RING];
+    auto load_ka = [&](int k) { ka[k % RING] = read_k(bk, k % JT, k / JT); };
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) nxt[jt][i] = 0.f;
+#pragma unroll
+    for (int k = 0; k < RING; ++k) load_ka(k);
+    fence();
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+      nxt[k % JT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ka[k % RING], qf[k / JT], nxt[k % JT], 0, 0, 0);
+      if (k + RING < NS) load_ka(k + RING);
+      else if (k + RING - NS < DT) load_va(bv, k + RING - NS);
+#pragma unroll
+      for (int e = 0; e < EPO; e += 2) prob2(cur, EPO * k + e);
+      fence();
+    }
+  };
+  // Step i computes P and the O update of unit i (in this group's order) and
+  // the scores of unit i + 1. At its barrier K(i + 1) and V(i) are in LDS; it
+  // requests K(i + 2) and V(i + 1) into the tiles K(i) and V(i - 1) left free.
+  auto landed = [&]() {  // everything requested has arrived, in every wavefront
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  };
+  auto next = [&]() {
+    turn_window();
+    return fetch();
+  };
+  const Unit d0 = next();
+  issue_k(d0, 0);
+  issue_v(d0, 0);
+  Unit d1 = next(), d2;  // units i + 1 and i + 2 of step i
+  issue_k(d1, 1);
+  turn_window();
+  // q's loads are complete here on every path, so the loop's matrix ops never
+  // wait on the memory counter (which would also wait for the rows just
+  // requested)
+#pragma unroll
+  for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qf[s]));
+  floatx16 sA[JT], sB[JT];
+  landed();
+  if (n_see > 0) {
+    scores(sA, 0);
+    rowmax(sA);
+    mask(sA, d0);
+    refmax();
+  }
+  // B0, the tile of unit i, is a constant, so that every LDS address is a
+  // register fixed for the whole call plus an immediate offset
+  auto step = [&](auto b0c, int i, floatx16 (&cur)[JT], floatx16 (&nxt)[JT]) {
+    constexpr int b0 = decltype(b0c)::value, b1 = 1 - b0;
+    landed();  // (step 0: K(0) has been read)
+    d2 = fetch();
+    issue_k(d2, b0);
+    issue_v(d1, b1);
+    if (i < n_see) {
+      scores_probs(cur, nxt, b1, b0);
+      // O^T += V^T P^T, and the next unit's row maxima
+      float c[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+      for (int k = 0; k < NO; ++k) {
+        acc[k % DT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[k % DT], pb[k / DT], acc[k % DT], 0, 0, 0);
+        if (k + DT < NO) load_va(b0, k + DT);
+        constexpr int EM = 16 * JT / NO;  // elements of the maximum per op
+#pragma unroll
+        for (int e = EM * k; e < EM * (k + 1); ++e) c[k % 4] = fmaxf(c[k % 4], nxt[e / 16][e % 16]);
+        fence();
+      }
+      lmax = fmaxf(fmaxf(c[0], c[1]), fmaxf(c[2], c[3]));
+      mask(nxt, d1);
+      refmax();
+    }
+    turn_window();
+    d1 = d2;
+  };
+  for (int i = 0; i < steps; i += 2) {
+    step(std::integral_constant<int, 0>{}, i, sA, sB);
+    if (i + 1 < steps) step(std::integral_constant<int, 1>{}, i + 1, sB, sA);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load writes LDS after this
+  // the row's sum over both halves of the wavefront
+  n_run += n2;
+  float n_row = n_run + __shfl_xor(n_run, 32);
+  const int r = 32 * w + l32;  // row inside the tile
+  if constexpr (KG > 1) {
+    float* ob = reinterpret_cast<float*>(lds);  // [KG-1][QR][OST]
+    float* mb = ob + (KG - 1) * QR * OST;       // [KG-1][QR][2]
+    __syncthreads();
+    if (grp > 0) {
+      float* o_ = ob + ((grp - 1) * QR + r) * OST + 4 * hl;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          *reinterpret_cast<floatx4*>(o_ + 32 * dt + 8 * b) =
+              floatx4{acc[dt][4 * b], acc[dt][4 * b + 1], acc[dt][4 * b + 2], acc[dt][4 * b + 3]};
+      if (hl == 0) {
+        mb[((grp - 1) * QR + r) * 2] = m_run;
+        mb[((grp - 1) * QR + r) * 2 + 1] = n_row;
+      }
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int k = 1; k < KG; ++k) {
+        const float mo = mb[((k - 1) * QR + r) * 2], no = mb[((k - 1) * QR + r) * 2 + 1];
+        const float M = fmaxf(m_run, mo);
+        const float ws = fast_exp2(m_run - M), wo = fast_exp2(mo - M);
+        const float* o_ = ob + ((k - 1) * QR + r) * OST + 4 * hl;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const floatx4 x = *reinterpret_cast<const floatx4*>(o_ + 32 * dt + 8 * b);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[dt][4 * b + i] = acc[dt][4 * b + i] * ws + x[i] * wo;
+          }
+        n_row = n_row * ws + no * wo;
+        m_run = M;
+      }
+    }
+  }
+  if (grp > 0 || qi >= n_q) return;
+  const float inv = 1.f / n_row;
+  _Float16* out = P.o + (static_cast<size_t>(qi) * H + h) * D + 4 * hl;
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      half4 r4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r4[i] = static_cast<_Float16>(acc[dt][4 * b + i] * inv);
+      *reinterpret_cast<half4*>(out + 32 * dt + 8 * b) = r4;
+    }
+}
+
+template <int D, int QW, int KG, int TOK>
+void launch_wide(const KpfParams& P, const PrefillArgs& a, hipStream_t stream) {
+  constexpr int kLaneChunks = 64;
+  const int blocks = (a.n_q + 32 * QW - 1) / (32 * QW) * a.H;
+  const dim3 grid(8 * ((blocks + 7) / 8)), block(64 * QW * KG);  // a multiple of the XCD count
+  if (a.host_path && a.n_chunks <= kLaneChunks) {
+    KpfPath<kLaneChunks> path;
+    for (int j = 0; j < a.n_chunks; ++j) path.slot[j] = a.host_path[j];
+    for (int j = 0; j <= a.n_chunks; ++j) path.start[j] = a.host_path[a.n_chunks + j];
+    kpw_kernel<D, QW, KG, TOK, kLaneChunks><<<grid, block, 0, stream>>>(P, nullptr, nullptr, path);
+  } else if (a.host_path) {
+    KpfPath<kPrefillInlineChunks> path;
+    for (int j = 0; j < a.n_chunks; ++j) path.slot[j] = a.host_path[j];
+    for (int j = 0; j <= a.n_chunks; ++j) path.start[j] = a.host_path[a.n_chunks + j];
+    kpw_kernel<D, QW, KG, TOK, kPrefillInlineChunks><<<grid, block, 0, stream>>>(P, nullptr, nullptr, path);
+  } else {
+    const KpfPath<1> none{};
+    kpw_kernel<D, QW, KG, TOK, 0><<<grid, block, 0, stream>>>(P, a.chunk_slot, a.chunk_start, none);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
@@ -578,9 +1039,22 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
   KpfParams P{static_cast<const _Float16*>(a.q), static_cast<_Float16*>(a.o),
               static_cast<const _Float16*>(a.kpool), static_cast<const _Float16*>(a.vpool), a.ss,
               a.hs, a.n_chunks, a.n_q, a.H, a.C, a.qscale, a.n_split, a.ws, a.cnt, a.cnt_shift,
-              static_cast<uint32_t>(a.ws_bytes)};
+              static_cast<uint32_t>(a.ws_bytes), a.L};
   if (a.n_split < 1 || (a.n_split > 1 && (!a.ws || !a.cnt || a.ws_bytes > 0xFFFFFFF0ull)))
     return hipErrorInvalidValue;
+  if (a.host_path ? a.n_chunks > kPrefillInlineChunks : !a.chunk_slot) return hipErrorInvalidValue;
+  if (a.tile_rows == 128 && a.n_split == 1) {
+    if (a.D == 128) launch_wide<128, 4, 1, 64>(P, a, stream);
+    else if (a.D == 64) launch_wide<64, 4, 1, 64>(P, a, stream);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
+  if (a.tile_rows == 64 && a.n_split == 1) {
+    if (a.D == 128) launch_wide<128, 2, 2, 32>(P, a, stream);
+    else if (a.D == 64) launch_wide<64, 2, 2, 32>(P, a, stream);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
   // two groups of four wavefronts (16 queries each), 64-row units, two LDS
   // tiles per group
   constexpr int kGroups = 2, kWaves = 4, kTok = 64;

@@ -1,0 +1,75 @@
+"""Prefill with 32-query wavefronts (joins whose query tiles give every compute
+unit a block): both tile sizes, ragged tiles, chunks of 1 to 130 tokens (paths
+in the argument table, past one 64-chunk window, and on the device), short
+chunks mid-path, both head sizes and layouts, against the oracle. The pool is
+poisoned with NaN first, so a row read past a chunk's length shows."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import prefill_attention
+from parity_util import Pair, assert_close, to_dev
+from workloads import prefix_keyed_kv
+
+pytestmark = pytest.mark.gpu
+
+
+# heads x ceil(n_q / 128) >= 256 blocks: 128-query tiles; else, if heads x
+# ceil(n_q / 64) >= 256, 64-query tiles (256 compute units)
+@pytest.mark.parametrize("c,d,H,prefix,n_q,layout", [
+    (64, 128, 128, 100, 129, "interleaved"),   # 128-query tiles, the last of one query
+    (64, 64, 256, 0, 77, "split"),             # one 128-query tile, nothing cached
+    (16, 128, 128, 37, 200, "interleaved"),    # a short chunk mid-path
+    (130, 64, 128, 300, 140, "split"),         # three units a chunk, the last of two rows
+    (3, 128, 128, 50, 250, "interleaved"),     # 100 chunks: past one window
+    (1, 64, 256, 200, 100, "split"),           # 300 chunks: device table
+    (64, 128, 128, 100, 65, "split"),          # 64-query tiles, two key groups
+    (16, 64, 128, 1, 128, "interleaved"),      # 64-query tiles, 32-row units
+    (100, 128, 256, 5, 20, "interleaved"),     # 128-query tile, mostly past n_q
+    (7, 128, 130, 400, 70, "split"),           # 64-query tiles past one window
+    (2, 64, 128, 460, 90, "interleaved"),      # 275 chunks, 64-query tiles
+    (200, 128, 128, 30, 100, "split"),         # 64-query tiles, seven 32-row units a chunk
+    (64, 64, 128, 30, 128, "split"),           # d = 64, 256 64-query tiles: 16-query blocks
+])
+def test_wide_tiles(c, d, H, prefix, n_q, layout):
+    print(f"[case] prefill wide c={c} d={d} H={H} prefix={prefix} n_q={n_q} {layout}", flush=True)
+    rng = np.random.default_rng(c * 1000 + n_q)
+    p = Pair(c, H, d, np.float16, 2 * (prefix + n_q) // c + 80, layout=layout)
+    for pool in (p.cache.k_pool, p.cache.v_pool):
+        pool.fill_(float("nan"))
+    pre = rng.integers(0, 50, prefix).astype(np.int32)
+    for sid, tail in ((0, np.full(9, 60)), (1, rng.integers(70, 90, n_q))):
+        toks = np.concatenate([pre, tail]).astype(np.int32)
+        k, v = prefix_keyed_kv(5, toks, 0, H, d, np.float16)
+        p.insert(sid, toks, k, v)
+    q = rng.standard_normal((n_q, H, d)).astype(np.float16)
+    rows = sorted({0, n_q - 1, n_q // 2, min(63, n_q - 1), min(64, n_q - 1), min(31, n_q - 1)}
+                  | {int(x) for x in rng.integers(0, n_q, 6)})
+    for scale in (0.0, 0.4):
+        o = p.cache.prefill(1, to_dev(q), scale=scale).cpu().numpy()
+        ref = prefill_attention(p.tree, 1, q, scale or 1.0 / np.sqrt(d), queries=rows)
+        assert_close(o[rows], ref, np.float16, f"wide c={c} d={d} H={H} n_q={n_q} scale={scale}")
+        assert np.isfinite(o).all()
+
+
+def test_moving_reference_maximum():
+    """Scores that grow along the path by far more than the slack of the
+    softmax reference: every unit moves it."""
+    print("[case] prefill wide spikes", flush=True)
+    c, d, H, n_q = 64, 128, 128, 150
+    rng = np.random.default_rng(3)
+    p = Pair(c, H, d, np.float16, 40)
+    n = 500
+    toks = np.arange(n, dtype=np.int32)
+    k = (rng.standard_normal((n, H, d)) * np.linspace(0.05, 2, n)[:, None, None]).astype(np.float16)
+    v = rng.standard_normal((n, H, d)).astype(np.float16)
+    p.insert(0, toks, k, v)
+    q = (3 * rng.standard_normal((n_q, H, d))).astype(np.float16)
+    o = p.cache.prefill(0, to_dev(q), scale=0.2).cpu().numpy()
+    rows = [0, 1, 31, 32, 100, 127, 128, 149]
+    ref = prefill_attention(p.tree, 0, q, 0.2, queries=rows)
+    # a peaked softmax passes single V rows through: fp16 rounding of values up
+    # to ~4.5 (half an ulp 2e-3) on top of the probabilities' own
+    err = np.abs(o[rows].astype(np.float64) - ref)
+    print(f"[parity] spikes max_abs={err.max():.3e}", flush=True)
+    assert (err <= 2e-3 + 2.0 ** -10 * np.abs(ref)).all()

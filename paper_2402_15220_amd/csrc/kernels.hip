@@ -35,6 +35,7 @@
 
 #include <cfloat>
 #include <cstdint>
+#include <type_traits>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -279,7 +280,14 @@ constexpr int ksf_lds_bytes() {
   return 4 * (D * sizeof(T) / 16) * (16 / static_cast<int>(sizeof(T)) + 2) * 4;
 }
 
-template <typename T, int D>
+// SM (chunks of at most 32 tokens): a step gathers its 64 tokens from
+// 64 / C consecutive chunks, each lane's loads from the chunk its tokens fall
+// into, so all of a step's loads are for tokens of the row (a step of one
+// 16-token chunk loaded and computed 48 masked ones). With the chunk-first
+// side's chunks_at_once: 48 rows over a 1,000-token prompt with 200 to 600
+// private tokens in 16-token chunks 87 -> 59 us (5.6 TB/s), one row of 32,765
+// tokens (8 heads) 54 -> 29, in 32-token chunks 32 rows 54 -> 51.
+template <typename T, int D, bool SM>
 __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, char* lds) {
   using E = Elem<T>;
   constexpr int EPL = E::kPerVec;
@@ -337,8 +345,35 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
   // is known, as if the chunk were full (rows clamped to the tile, so in
   // bounds); a shorter chunk is requested again with the right clamp below
   // (rows past its length may hold anything, even NaN, and are never used).
-  if (n_chunks > 0) load_step(kr, vr, it.slot[0], 0, cm);
+  // small chunks: token u of a step is row srow[u] of its chunk schk[u]
+  int schk[SM ? U : 1], srow[SM ? U : 1];
+  const int G = SM ? 64 / C : 1;  // chunks per step
+  auto load_small = [&](int slots, int lens, int j, int gn) {  // lanes: slot and length of chunk i
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(j + min(schk[u], G - 1), gn - 1);
+      const int sl = __shfl(slots, i), ln = __shfl(lens, i);
+      const size_t off = static_cast<size_t>(sl) * slot_stride + static_cast<size_t>(min(srow[u], ln - 1)) * D;
+      kr[u] = *reinterpret_cast<const uint4*>(kpool + off);
+      vr[u] = __builtin_bit_cast(
+          uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vpool + off)));
+    }
+  };
   const int gn0 = min(64, n_chunks);
+  if constexpr (SM) {
+    const int magic = (65536 + C - 1) / C;  // x / C == x * magic >> 16 for x < 64, C <= 32
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int tok = u * TPS + tok_off;
+      schk[u] = tok * magic >> 16;
+      srow[u] = tok - schk[u] * C;
+    }
+    // as below: before the lengths are known, as if the chunks were full; the
+    // record's inline slots cover the first step of chunks of 8 or more
+    if (n_chunks > 0 && G <= kSfInline) load_small(slot_lo, cm, 0, gn0);
+  } else {
+    if (n_chunks > 0) load_step(kr, vr, it.slot[0], 0, cm);
+  }
   int slot_hi = 0;
   if (lane >= it.n_inline && lane < gn0) slot_hi = P.priv_slot[it.cb + lane];
   const uint4 qr = *reinterpret_cast<const uint4*>(static_cast<const T*>(P.q) +
@@ -347,8 +382,8 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
   const int np = it.part_e - it.part_b;
   int pidx = -1;
   if (w == 0 && lane < np && np <= 64) pidx = P.parts[it.part_b + lane];
-  const int len0 = n_chunks > 0 ? P.slot_len[it.slot[0]] : 0;
-  int len_lo = lane < it.n_inline ? P.slot_len[slot_lo] : 0;
+  const int len0 = !SM && n_chunks > 0 ? P.slot_len[it.slot[0]] : 0;
+  int len_lo = !SM && lane < it.n_inline ? P.slot_len[slot_lo] : 0;
   float qf[EPL];
   E::unpack(qr, qf);
 
@@ -357,7 +392,7 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
   for (int j = 0; j < EPL; ++j) acc[j] = 0.f;
 
   // online softmax over one 64-token step (Eqn 1 for the step, folded by Eqn 2)
-  auto do_step = [&](const uint4* kr_, const uint4* vr_, int t0, int len) {
+  auto do_step = [&](const uint4* kr_, const uint4* vr_, auto visible) {
     float s[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -371,8 +406,7 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
     float mx = kNegBig;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int tok = t0 + u * TPS + tok_off;
-      s[u] = tok < len ? s[u] * P.qscale : -INFINITY;
+      s[u] = visible(u) ? s[u] * P.qscale : -INFINITY;
       mx = fmaxf(mx, s[u]);
     }
     const float mn = fmaxf(m, mx);
@@ -392,14 +426,14 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
     m = mn;
   };
 
-  if (n_chunks > 0) {
+  if (!SM && n_chunks > 0) {
     // chunks are taken 64 at a time: lane i holds the slot and length of
     // chunk i of the group, broadcast with readlane; in the first group the
     // first kSfInline come from the record (slot_lo, len_lo) and the others
     // from priv_slot (slot_hi, len_hi), so the early chunks never wait for
     // the later ones' lengths
     if (len0 < cm) load_step(kr, vr, it.slot[0], 0, len0);  // uniform; rare
-    do_step(kr, vr, 0, len0);
+    do_step(kr, vr, [&](int u) { return u * TPS + tok_off < len0; });
     int len_hi = 0;
     if (lane >= it.n_inline && lane < gn0) len_hi = P.slot_len[slot_hi];
     int jj = 0, t0 = 64, len = len0, slot = it.slot[0];
@@ -412,7 +446,7 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
         t0 = 0;
       }
       load_step(kr, vr, slot, t0, len);
-      do_step(kr, vr, t0, len);
+      do_step(kr, vr, [&](int u) { return t0 + u * TPS + tok_off < len; });
       t0 += 64;
     }
     for (int g0 = it.cb + 64; g0 < it.ce; g0 += 64) {
@@ -427,8 +461,38 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
         const int ln = __builtin_amdgcn_readlane(my_len, j);
         for (int tt = 0; tt < ln; tt += 64) {
           load_step(kr, vr, sl, tt, ln);
-          do_step(kr, vr, tt, ln);
+          do_step(kr, vr, [&](int u) { return tt + u * TPS + tok_off < ln; });
         }
+      }
+    }
+  }
+
+  if constexpr (SM) {
+    // 64 chunks at a time, slots and lengths one per lane
+    for (int g0 = 0; g0 < n_chunks; g0 += 64) {
+      const int gn = min(64, n_chunks - g0);
+      int slots, lens;
+      if (g0 == 0) {
+        slots = lane < it.n_inline ? slot_lo : slot_hi;
+        lens = lane < gn ? P.slot_len[slots] : 0;
+      } else {
+        slots = P.priv_slot[it.cb + g0 + min(lane, gn - 1)];
+        lens = lane < gn ? P.slot_len[slots] : 0;
+      }
+      for (int j = 0; j < gn; j += G) {
+        // token u is there: its chunk is in the step and in the group, and long
+        // enough (an absent token reads a row of a chunk that is there)
+        bool in[U];
+        bool again = g0 > 0 || j > 0 || G > kSfInline;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool shorter = srow[u] >= __shfl(lens, min(j + min(schk[u], G - 1), gn - 1));
+          in[u] = schk[u] < G && j + schk[u] < gn && !shorter;
+          again |= shorter;
+        }
+        // a short chunk: its rows past the length may hold anything, even NaN
+        if (__any(again)) load_small(slots, lens, j, gn);
+        do_step(kr, vr, [&](int u) { return in[u]; });
       }
     }
   }
@@ -805,6 +869,13 @@ __device__ __forceinline__ void cf_publish(const KcfParams& P, const CfSeg& sg, 
   if (P.cnt) cf_arrive<OUT_T, D, R>(P, rb, nrows, h, reinterpret_cast<float (*)[R]>(mbuf), fl);
 }
 
+// Chunks a chunk-first chain's four wavefronts work on at once: a wavefront
+// takes 16 tokens, so chunks of up to 16 tokens go one to a wavefront, of up
+// to 32 one to a pair; with longer ones the four share each chunk. (One
+// 16-token chunk per chain left three of four wavefronts idle: 32 identical
+// sequences of 2,048 tokens took 21 us so, 12.4 us now.)
+__device__ __forceinline__ int chunks_at_once(int C) { return C <= 16 ? 4 : C <= 32 ? 2 : 1; }
+
 // Lazy reference maximum of the chunk-first softmax (log2 units): P <= 2^8.
 constexpr float kLazyMax = 8.f;
 
@@ -852,8 +923,12 @@ __device__ __forceinline__ void kcf_f16_block(const KcfParams& P, int seg, int z
   constexpr int TPL = 64 / GPR;   // tokens per wavefront load
   constexpr int NVL = 16 / TPL;   // V loads per lane per block
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wq = w & 3;                                       // token quarter of a block
-  const int chain = __builtin_amdgcn_readfirstlane(w >> 2);  // chain (wave-uniform)
+  // chain (wave-uniform): takes chunks chain, chain + stride, ...; wq: this
+  // wavefront's 16-token slice of them
+  const int at_once = chunks_at_once(P.C), stride = NCH * at_once;
+  const int wpc = 4 / at_once;
+  const int chain = __builtin_amdgcn_readfirstlane((w >> 2) * at_once + (w & 3) / wpc);
+  const int wq = (w & 3) % wpc;
   const int l16 = lane & 15, g = lane >> 4;
   _Float16* vw = reinterpret_cast<_Float16*>(lds) + w * 16 * RS;
 
@@ -936,7 +1011,7 @@ __device__ __forceinline__ void kcf_f16_block(const KcfParams& P, int seg, int z
     c.t0 += 64;
     if (c.t0 >= c.len) {
       c.t0 = 0;
-      c.j += NCH;
+      c.j += stride;
       if (c.j < nch) {
         c.slot = __builtin_amdgcn_readlane(my_slot, c.j);
         c.len = __builtin_amdgcn_readlane(my_len, c.j);
@@ -1123,8 +1198,12 @@ __device__ __forceinline__ void kcf_f32_block(const KcfParams& P, int seg, int z
   constexpr int R = 16 * NRT;
   constexpr int BIG = 4 * NCH * R * (D + 4) * 4;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wq = w & 3;                                       // token quarter of a block
-  const int chain = __builtin_amdgcn_readfirstlane(w >> 2);  // chain (wave-uniform)
+  // chain (wave-uniform): takes chunks chain, chain + stride, ...; wq: this
+  // wavefront's 16-token slice of them
+  const int at_once = chunks_at_once(P.C), stride = NCH * at_once;
+  const int wpc = 4 / at_once;
+  const int chain = __builtin_amdgcn_readfirstlane((w >> 2) * at_once + (w & 3) / wpc);
+  const int wq = (w & 3) % wpc;
   const int l16 = lane & 15, g = lane >> 4;
 
   const CfSeg sg = P.segs[seg];
@@ -1214,7 +1293,7 @@ __device__ __forceinline__ void kcf_f32_block(const KcfParams& P, int seg, int z
     int jn = j, tn = t0 + 64, sn = slot, ln = len;
     if (tn >= len) {
       tn = 0;
-      jn += NCH;
+      jn += stride;
       if (jn < nch) {
         sn = __builtin_amdgcn_readlane(my_slot, jn);
         ln = __builtin_amdgcn_readlane(my_len, jn);
@@ -1384,7 +1463,7 @@ constexpr int tpp_blocks_per_cu() {
   return sizeof(T) == 4 && D == 128 ? 3 : 4;
 }
 
-template <typename T, int D, int NRT>
+template <typename T, int D, int NRT, bool SM>
 __global__ __launch_bounds__(256, (tpp_blocks_per_cu<T, D>())) void tpp_kernel(TppParams P) {
   __shared__ __attribute__((aligned(16))) char lds[tpp_lds_bytes<T, D, NRT>()];
   const int b = static_cast<int>(blockIdx.x);
@@ -1400,7 +1479,7 @@ __global__ __launch_bounds__(256, (tpp_blocks_per_cu<T, D>())) void tpp_kernel(T
       kcf_f32_block<D, NRT>(P.cf, seg, z, h, lds);
   } else {
     const int bb = b - P.n_cf;
-    ksf_block<T, D>(P.sf, bb / H, bb % H, lds);
+    ksf_block<T, D, SM>(P.sf, bb / H, bb % H, lds);
   }
 }
 
@@ -1440,14 +1519,14 @@ __global__ __launch_bounds__(256 * kDeepChains) void kcf_deep_kernel(KcfParams P
     kcf_f32_block<D, 1, float, kDeepChains>(P, rest / zb, rest % zb, h, lds);
 }
 
-template <typename T, int D>
+template <typename T, int D, bool SM>
 __global__ __launch_bounds__(256) void ksf_kernel(KsfParams P) {
   __shared__ __attribute__((aligned(16))) char lds[ksf_lds_bytes<T, D>()];
   const int b = static_cast<int>(blockIdx.x);
-  ksf_block<T, D>(P, b / P.H, b % P.H, lds);
+  ksf_block<T, D, SM>(P, b / P.H, b % P.H, lds);
 }
 
-template <typename T, int D, int NRT>
+template <typename T, int D, int NRT, bool SM>
 hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, hipStream_t s,
                          const SideStream& side, const int32_t* group_ptr, int n_groups) {
   const bool both = (mask & 3) == 3;
@@ -1459,7 +1538,7 @@ hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, h
         return hipSuccess;
       }
       const int grid = P.n_cf + n_sf;
-      if (grid > 0) tpp_kernel<T, D, NRT><<<grid, 256, 0, s>>>(P);
+      if (grid > 0) tpp_kernel<T, D, NRT, SM><<<grid, 256, 0, s>>>(P);
       return hipSuccess;
     } else {
       return hipErrorInvalidValue;
@@ -1473,7 +1552,7 @@ hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, h
     if ((e = hipStreamWaitEvent(side.stream, side.fork, 0)) != hipSuccess) return e;
     kcf_kernel<T, D, NRT><<<P.n_cf, 256, 0, side.stream>>>(P.cf, P.zb);
     if ((e = hipEventRecord(side.join, side.stream)) != hipSuccess) return e;
-    ksf_kernel<T, D><<<n_sf, 256, 0, s>>>(P.sf);
+    ksf_kernel<T, D, SM><<<n_sf, 256, 0, s>>>(P.sf);
     return hipStreamWaitEvent(s, side.join, 0);
   }
   // phases one after another on the caller's stream; arrival counting only
@@ -1500,11 +1579,11 @@ hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, h
   } else if ((mask & 1) && P.n_cf > 0) {
     kcf_kernel<T, D, NRT><<<P.n_cf, 256, 0, s>>>(cf, P.zb);
   }
-  if ((mask & 2) && n_sf > 0) ksf_kernel<T, D><<<n_sf, 256, 0, s>>>(sf);
+  if ((mask & 2) && n_sf > 0) ksf_kernel<T, D, SM><<<n_sf, 256, 0, s>>>(sf);
   return hipSuccess;
 }
 
-template <typename T, int D>
+template <typename T, int D, bool SM>
 hipError_t launch_all(const AttnArgs& a, const DevWork& w, hipStream_t s, int mask,
                       const SideStream& side) {
   TppParams P;
@@ -1528,8 +1607,8 @@ hipError_t launch_all(const AttnArgs& a, const DevWork& w, hipStream_t s, int ma
   P.n_cf = w.n_segs * P.zb * a.H;
   const int n_sf = w.n_items * a.H;
   hipError_t e;
-  if (nrt == 1) e = launch_phases<T, D, 1>(P, n_sf, w.schedule, mask, s, side, w.seg_group_ptr, w.n_seg_groups);
-  else e = launch_phases<T, D, 2>(P, n_sf, w.schedule, mask, s, side, w.seg_group_ptr, w.n_seg_groups);
+  if (nrt == 1) e = launch_phases<T, D, 1, SM>(P, n_sf, w.schedule, mask, s, side, w.seg_group_ptr, w.n_seg_groups);
+  else e = launch_phases<T, D, 2, SM>(P, n_sf, w.schedule, mask, s, side, w.seg_group_ptr, w.n_seg_groups);
   if (e != hipSuccess) return e;
   // Partial-writing schedules finish their rows inside the kernels; the merge
   // epilogue runs in the sequential schedule (split rows) or on its own.
@@ -1546,12 +1625,21 @@ hipError_t launch_all(const AttnArgs& a, const DevWork& w, hipStream_t s, int ma
 
 hipError_t launch_attention(const AttnArgs& a, const DevWork& w, hipStream_t s, int mask,
                             const SideStream& side) {
+  auto launch = [&](auto type, auto dim) -> hipError_t {
+    using T = decltype(type);
+    constexpr int D = decltype(dim)::value;
+    // chunks of at most 32 tokens: at least two fill a 64-token step
+    if (a.C <= 32) return launch_all<T, D, true>(a, w, s, mask, side);
+    return launch_all<T, D, false>(a, w, s, mask, side);
+  };
+  using D64 = std::integral_constant<int, 64>;
+  using D128 = std::integral_constant<int, 128>;
   if (a.dtype == 0) {
-    if (a.D == 128) return launch_all<_Float16, 128>(a, w, s, mask, side);
-    if (a.D == 64) return launch_all<_Float16, 64>(a, w, s, mask, side);
+    if (a.D == 128) return launch(_Float16{}, D128{});
+    if (a.D == 64) return launch(_Float16{}, D64{});
   } else {
-    if (a.D == 128) return launch_all<float, 128>(a, w, s, mask, side);
-    if (a.D == 64) return launch_all<float, 64>(a, w, s, mask, side);
+    if (a.D == 128) return launch(float{}, D128{});
+    if (a.D == 64) return launch(float{}, D64{});
   }
   return hipErrorInvalidValue;
 }

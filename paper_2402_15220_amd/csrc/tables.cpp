@@ -183,16 +183,20 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
   // us, 2-8-chunk segments 26-43 us; 96 rows over a 2048-token prompt with
   // one private chunk: 40 us against 55 us with 2-chunk segments).
   if (seg_chunks <= 0) {
+    // small chunks count in steps of as many as a block works on at once (the
+    // kernels' chunks_at_once)
+    const int32_t c = tree.chunk_size(), per_step = c <= 16 ? 4 : c <= 32 ? 2 : 1;
+    auto step_count = [per_step](int64_t chunks) { return (chunks + per_step - 1) / per_step; };
     int64_t work = 0;
     for (const auto& chain : runs) {
       const int64_t r = T.node_row_end[chain[0]] - T.node_row_begin[chain[0]];
-      work += static_cast<int64_t>(chain.size()) * ((r + 15) / 16) * num_heads;
+      work += step_count(static_cast<int64_t>(chain.size())) * ((r + 15) / 16) * num_heads;
     }
     int64_t priv_tokens = 0;
     for (int32_t k : T.priv_node) priv_tokens += T.node_len[k];
     int64_t max_priv = 0;
     for (int64_t r = 0; r < B; ++r)
-      max_priv = std::max<int64_t>(max_priv, T.priv_ptr[r + 1] - T.priv_ptr[r]);
+      max_priv = std::max<int64_t>(max_priv, step_count(T.priv_ptr[r + 1] - T.priv_ptr[r]));
     const double ksf_us = static_cast<double>(priv_tokens) * num_heads * token_head_bytes / 6.0e6;
     int64_t cap = std::min<int64_t>(64, std::max<int64_t>(16, static_cast<int64_t>(ksf_us / 3.0)));
     const int64_t cus = num_cus > 0 ? num_cus : 256;
@@ -205,7 +209,7 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
     // 47.0 us)
     int64_t quota = std::max<int64_t>(1, (work + cus - 1) / cus), pow2 = 1;
     while (pow2 < quota) pow2 <<= 1;
-    seg_chunks = static_cast<int32_t>(std::min<int64_t>(cap, pow2));
+    seg_chunks = static_cast<int32_t>(std::min<int64_t>(cap, pow2) * per_step);
   }
   if (seg_chunks > 64) seg_chunks = 64;  // the chunk-first kernel keeps a segment's slots in lanes
   W.seg_chunks = seg_chunks;

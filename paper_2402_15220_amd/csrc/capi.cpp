@@ -825,19 +825,34 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
   a.L = pos;
   const float sc = scale == 0.f ? 1.f / std::sqrt(static_cast<float>(a.D)) : scale;
   a.qscale = sc * 1.4426950408889634f;
-  // Key-range split: when the (64-query tile, head) blocks alone would leave
-  // compute units idle, cut each tile's units (64-row pieces of its chunks)
-  // into parts of at least six units, up to about one block per CU (one
-  // block fits a CU, so more blocks run in rounds): a part's time is mostly
-  // its block's fixed latency (start, first loads, merge, partial stores),
-  // so parts are kept long.
+  // Key-range split of the 16-query blocks: when the (64-query tile, head)
+  // blocks alone would leave compute units idle, cut each tile's units (64-row
+  // pieces of its chunks) into parts of at least six units, run by separate
+  // blocks. One block fits a compute unit, so more blocks than those run in
+  // rounds; a block takes a fixed ~5 us (start, first loads, merge, stores)
+  // and ~1.6 us per pair of units, a split ~1.5 us more and ~0.35 us per part
+  // for the fold. The part count is the one that model finds fastest (32
+  // heads, 1 / 2 / 3 / 4 parts: 130 queries over 1,154 positions 19.3 / 15.7 /
+  // 22.3 / 25.3 us, 300 over 1,324 22.4 / 30.6 / 27.2 / 37.3, 300 over 4,300
+  // 58.1 / 64.8 / 53.7 / 65.9; rounding the parts up to a block per compute
+  // unit took 22.7, 31.1 and 66.9).
   const int64_t tiles = (n_q + 63) / 64 * static_cast<int64_t>(a.H);
   const int64_t units = static_cast<int64_t>(nc) * ((a.C + 63) / 64);
   int64_t split = 1;
   if (cache->prefill_split > 0)
     split = cache->prefill_split;
-  else if (tiles < cache->num_cus)
-    split = std::min<int64_t>({(cache->num_cus + tiles - 1) / tiles, std::max<int64_t>(1, units / 6), 16});
+  else if (tiles < cache->num_cus) {
+    double best = 0;
+    for (int64_t k = 1; k <= std::min<int64_t>(std::max<int64_t>(1, units / 6), 16); ++k) {
+      const int64_t rounds = (tiles * k + cache->num_cus - 1) / cache->num_cus;
+      const int64_t pairs = (units + 2 * k - 1) / (2 * k);
+      const double us = rounds * (5.0 + 1.6 * pairs) + (k > 1 ? 1.5 + 0.35 * k : 0.0);
+      if (k == 1 || us < best) {
+        best = us;
+        split = k;
+      }
+    }
+  }
   a.n_split = static_cast<int>(split);
   // 32-query wavefronts wherever their tiles give every compute unit a block:
   // 128-query tiles (each K/V element through the caches once per 128
@@ -848,10 +863,15 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
   // 1,200 38.2 / 27.9 / 27.1, 512 over 1,536 24.9 / 24.8 / 31.0, the same in
   // 16-token chunks 61.1 / 34.8 / -, 300 over 300 9.3 / 9.7 / 10.6, 200 over
   // 1,224 16.9 / 20.4 / 25.4. At d = 64 a 64-query tile has too little work per
-  // unit: 16 heads, 1,024 over 2,024 20.0 / 21.8 us.
+  // unit: 16 heads, 1,024 over 2,024 20.0 / 21.8 us. Small chunks gain more
+  // from the 32-row units than the split gives, from half the compute units
+  // on (300 queries over 1,324 positions in 16-token chunks: 79 us in one part,
+  // 65 in three, 44 with 64-query tiles).
+  if (cache->prefill_split == 0 && a.C <= 32 && 2 * tiles >= cache->num_cus) split = a.n_split = 1;
   if (split == 1) {
     if ((n_q + 127) / 128 * a.H >= cache->num_cus) a.tile_rows = 128;
-    else if (tiles >= cache->num_cus && (a.D == 128 || a.C <= 32)) a.tile_rows = 64;
+    else if (a.C <= 32 ? 2 * tiles >= cache->num_cus : tiles >= cache->num_cus && a.D == 128)
+      a.tile_rows = 64;
   }
   if (split > 1) {
     const size_t ws = static_cast<size_t>(tiles * split) * ca::prefill_part_bytes(a.D);

@@ -29,6 +29,9 @@ pytestmark = pytest.mark.gpu
     (7, 128, 130, 400, 70, "split"),           # 64-query tiles past one window
     (2, 64, 128, 460, 90, "interleaved"),      # 275 chunks, 64-query tiles
     (200, 128, 128, 30, 100, "split"),         # 64-query tiles, seven 32-row units a chunk
+    (64, 128, 32, 1030, 130, "interleaved"),   # 16-query blocks: two parts, one round
+    (64, 128, 32, 4000, 300, "split"),         # three parts, two rounds
+    (16, 128, 32, 500, 257, "interleaved"),    # small chunks: 64-query tiles from half the chip on
     (64, 64, 128, 30, 128, "split"),           # d = 64, 256 64-query tiles: 16-query blocks
 ])
 def test_wide_tiles(c, d, H, prefix, n_q, layout):

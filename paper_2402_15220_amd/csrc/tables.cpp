@@ -209,6 +209,15 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
     // 47.0 us)
     int64_t quota = std::max<int64_t>(1, (work + cus - 1) / cus), pow2 = 1;
     while (pow2 < quota) pow2 <<= 1;
+    // at most about 16 segments a run: a tree too small to fill the chip would
+    // else be cut to single chunks, and folding a partial per chunk costs more
+    // than the shorter chains save (8 rows, one head, 64 shared chunks: 18.9
+    // us in 64 segments, 12.8 in 32, 10.7 in 16, 11.2 in 8; 16 rows, 8 heads,
+    // 32 shared chunks 10.6 in 32, 10.3 in 16, 11.5 in 8)
+    int64_t longest = 0;
+    for (const auto& chain : runs)
+      longest = std::max<int64_t>(longest, step_count(static_cast<int64_t>(chain.size())));
+    while (pow2 * 16 < longest && pow2 < 16) pow2 <<= 1;
     seg_chunks = static_cast<int32_t>(std::min<int64_t>(cap, pow2) * per_step);
   }
   if (seg_chunks > 64) seg_chunks = 64;  // the chunk-first kernel keeps a segment's slots in lanes

@@ -93,6 +93,26 @@ def test_static_scratch_never_outgrown_by_the_split(H, parts):
     B.ca_destroy(h)
 
 
+# shared runs of a tree too small to fill the chip: at most about 16 segments a
+# run, counted in steps of as many small chunks as a block works on at once
+@pytest.mark.parametrize("c,H,rows,prompt,seg", [
+    (64, 1, 8, 64 * 16, 1),      # 16 chunks: a quota of one, 16 segments
+    (64, 1, 8, 64 * 17, 2),
+    (64, 1, 8, 64 * 64, 4),
+    (64, 1, 8, 64 * 1000, 16),   # no longer than that for its own sake
+    (16, 1, 8, 16 * 64, 4),      # 16 steps of four chunks
+    (16, 1, 8, 16 * 65, 8),
+    (32, 1, 8, 32 * 64, 4),      # 32 steps of two
+])
+def test_smallest_segments(c, H, rows, prompt, seg):
+    h = _table_cache(c, H, 64)
+    for sid in range(rows):
+        B.ca_insert(h, sid, list(range(prompt)) + [100_000 + sid])
+    B.ca_workspace_size(h)
+    assert B.ca_stats(h)["seg_chunks"] == seg
+    B.ca_destroy(h)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("c,H,d,dt,prompt,lens", [
     (64, 2, 128, np.float16, 0, [64 * 6 + 1]),

@@ -839,40 +839,44 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
   const int64_t tiles = (n_q + 63) / 64 * static_cast<int64_t>(a.H);
   const int64_t units = static_cast<int64_t>(nc) * ((a.C + 63) / 64);
   int64_t split = 1;
-  if (cache->prefill_split > 0)
+  const int64_t cus = cache->num_cus;
+  double best_us = 0;
+  if (cache->prefill_split > 0) {
     split = cache->prefill_split;
-  else if (tiles < cache->num_cus) {
-    double best = 0;
-    for (int64_t k = 1; k <= std::min<int64_t>(std::max<int64_t>(1, units / 6), 16); ++k) {
-      const int64_t rounds = (tiles * k + cache->num_cus - 1) / cache->num_cus;
+  } else {
+    const int64_t most = tiles < cus ? std::min<int64_t>(std::max<int64_t>(1, units / 6), 16) : 1;
+    for (int64_t k = 1; k <= most; ++k) {
+      const int64_t rounds = (tiles * k + cus - 1) / cus;
       const int64_t pairs = (units + 2 * k - 1) / (2 * k);
       const double us = rounds * (5.0 + 1.6 * pairs) + (k > 1 ? 1.5 + 0.35 * k : 0.0);
-      if (k == 1 || us < best) {
-        best = us;
+      if (k == 1 || us < best_us) {
+        best_us = us;
         split = k;
       }
     }
   }
-  a.n_split = static_cast<int>(split);
   // 32-query wavefronts wherever their tiles give every compute unit a block:
   // 128-query tiles (each K/V element through the caches once per 128
-  // queries), else 64-query ones, which also move small chunks in 32-row
-  // units instead of 64; smaller joins are latency-bound and keep the 16-query
-  // blocks and their key-range split. 32 heads, 16-query / 64 / 128-query
+  // queries), else 64-query ones; smaller joins are latency-bound and keep the
+  // 16-query blocks and their key-range split. 32 heads, 16-query / 64 / 128-query
   // blocks: 1,100 queries over 1,100 positions 38.2 / 25.9 / 27.2 us, 900 over
-  // 1,200 38.2 / 27.9 / 27.1, 512 over 1,536 24.9 / 24.8 / 31.0, the same in
-  // 16-token chunks 61.1 / 34.8 / -, 300 over 300 9.3 / 9.7 / 10.6, 200 over
-  // 1,224 16.9 / 20.4 / 25.4. At d = 64 a 64-query tile has too little work per
-  // unit: 16 heads, 1,024 over 2,024 20.0 / 21.8 us. Small chunks gain more
-  // from the 32-row units than the split gives, from half the compute units
-  // on (300 queries over 1,324 positions in 16-token chunks: 79 us in one part,
-  // 65 in three, 44 with 64-query tiles).
-  if (cache->prefill_split == 0 && a.C <= 32 && 2 * tiles >= cache->num_cus) split = a.n_split = 1;
-  if (split == 1) {
-    if ((n_q + 127) / 128 * a.H >= cache->num_cus) a.tile_rows = 128;
-    else if (a.C <= 32 ? 2 * tiles >= cache->num_cus : tiles >= cache->num_cus && a.D == 128)
+  // 1,200 38.2 / 27.9 / 27.1, 512 over 1,536 24.9 / 24.8 / 31.0, 300 over 300
+  // 9.3 / 9.7 / 10.6, 200 over 1,224 16.9 / 20.4 / 25.4. At d = 64 a 64-query
+  // tile has too little work per unit: 16 heads, 1,024 over 2,024 20.0 / 21.8 us.
+  // Over chunks of at most 32 tokens the 64-query tiles go wherever they are
+  // the faster by the same kind of model (two blocks a compute unit, ~0.87 us
+  // per pair of 32-row units, which hold two 16-token chunks; 300 queries over
+  // 1,300 positions in 16-token chunks: 80 us in one part of 16-query blocks,
+  // 65 in three, 23 so).
+  if (cache->prefill_split <= 1) {
+    const int64_t units32 = a.C == 16 ? (nc + 1) / 2 : static_cast<int64_t>(nc) * ((a.C + 31) / 32);
+    const double us64 = (tiles + 2 * cus - 1) / (2 * cus) * (5.0 + 0.87 * ((units32 + 1) / 2));
+    if ((n_q + 127) / 128 * a.H >= cus) a.tile_rows = 128;
+    else if (a.C <= 32 ? cache->prefill_split == 0 && us64 < best_us : tiles >= cus && a.D == 128)
       a.tile_rows = 64;
+    if (a.tile_rows > 0) split = 1;
   }
+  a.n_split = static_cast<int>(split);
   if (split > 1) {
     const size_t ws = static_cast<size_t>(tiles * split) * ca::prefill_part_bytes(a.D);
     if ((st = ensure_device(reinterpret_cast<char**>(&cache->d_pf_ws), &cache->d_pf_ws_cap, ws, s,

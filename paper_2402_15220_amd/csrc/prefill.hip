@@ -612,7 +612,13 @@ typedef float float2_t __attribute__((ext_vector_type(2)));
 // Tried, no faster: 256-query tiles (long prefixes 5% faster, others slower),
 // three or four LDS tiles, K/V staged through registers, offsetting one half
 // of the wavefronts by half a step.
-template <int D, int QW, int KG, int TOK, int NI>
+//
+// CC > 0: chunks of CC (16 or 32) tokens; a unit is the G = TOK / CC
+// consecutive chunks that fill it, each wavefront's load from the chunk its
+// rows fall into (a unit per 16-token chunk left three quarters of every unit
+// masked: 1,000 queries over 1,500 positions in 16-token chunks 128 -> 35.5 us,
+// in 32-token chunks 67 -> 32; 2,000 over 6,000 in 16-token chunks 827 -> 207).
+template <int D, int QW, int KG, int TOK, int CC, int NI>
 __global__ __launch_bounds__(64 * QW * KG, 2) void kpw_kernel(KpfParams P, const int32_t* __restrict__ cslot,
                                                               const int32_t* __restrict__ cstart,
                                                               const KpfPath<(NI > 0 ? NI : 1)> path) {
@@ -621,6 +627,7 @@ __global__ __launch_bounds__(64 * QW * KG, 2) void kpw_kernel(KpfParams P, const
   constexpr int DT = D / 32;        // 32-wide d tiles of O^T
   constexpr int NG = D / 8;         // 16-byte granules per token row
   constexpr int JT = TOK / 32;      // 32-token tiles of S^T per unit
+  constexpr int G = CC > 0 ? TOK / CC : 1;  // chunks per unit
   constexpr int RPI = 512 / D;      // token rows a wavefront's load moves (64 x 16 bytes)
   constexpr int LPT = TOK / RPI / QW;  // loads per wavefront and tile
   constexpr int TB = TOK * D * 2;   // LDS bytes of a K or V tile
@@ -704,34 +711,52 @@ __global__ __launch_bounds__(64 * QW * KG, 2) void kpw_kernel(KpfParams P, const
     if (n_ch < 64 * ++wi || 64 * wi >= nc) break;
     load_window(wi);
   }
-  const int n_units = n_ch * upc;  // at least one
+  const int n_units = CC > 0 ? (n_ch + G - 1) / G : n_ch * upc;  // at least one
   const int steps = (n_units + KG - 1) / KG;
   // steps of this group whose unit the wavefront sees something of (may be <= 0)
-  const int n_see = (n_vis * upc - grp + KG - 1) / KG;
+  const int n_see = ((CC > 0 ? (n_vis + G - 1) / G : n_vis * upc) - grp + KG - 1) / KG;
 
   struct Unit {
-    int64_t off;   // first row in a head's pool (elements)
-    int pos, len;  // first position, rows (<= 0: past a short chunk's end)
+    int64_t off[G];          // first row of each chunk in a head's pool (elements)
+    int cpos[G], clen[G];    // CC > 0: each chunk's first position and rows (0: past the path)
+    int pos, len;            // first position, rows (<= 0: past a short chunk's end); CC > 0:
+                             // len is negative when a chunk before the last is short
   };
   // descriptors of the group's units in order; past the end the last one again
   int fu = min(grp, n_units - 1);
-  int fj = upc == 1 ? fu : fu / upc, fr = upc == 1 ? 0 : fu - fj * upc;
+  int fj = CC > 0 ? fu * G : upc == 1 ? fu : fu / upc, fr = CC > 0 || upc == 1 ? 0 : fu - fj * upc;
   auto fetch = [&]() {  // after turn_window(); no branches
     Unit d;
-    const int l = fj & 63;
-    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(w_off), l);
-    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(w_off >> 32), l);
-    d.off = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo) + fr * (TOK * D);
-    d.pos = __builtin_amdgcn_readlane(w_start, l) + fr * TOK;
-    d.len = min(TOK, __builtin_amdgcn_readlane(w_end, l) - d.pos);
+    const int l0 = fj & 63;
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(w_off), l0 + q);
+      const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(w_off >> 32), l0 + q);
+      d.off[q] = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo) + fr * (TOK * D);
+      d.cpos[q] = __builtin_amdgcn_readlane(w_start, l0 + q) + fr * TOK;
+      d.clen[q] = min(TOK, __builtin_amdgcn_readlane(w_end, l0 + q) - d.cpos[q]);
+    }
+    d.pos = d.cpos[0];
+    d.len = d.clen[0];
+    bool whole = true;
+#pragma unroll
+    for (int q = 1; q < G; ++q) {
+      whole &= d.clen[q] == 0 || d.clen[q - 1] == CC;
+      d.len += d.clen[q];
+    }
+    d.len = whole ? d.len : -1;
     const bool more = fu + KG < n_units;
     fu += more ? KG : 0;
-    fr += more ? KG : 0;
+    if constexpr (CC > 0) {
+      fj += more ? KG * G : 0;
+    } else {
+      fr += more ? KG : 0;
 #pragma unroll
-    for (int k = 0; k < KG; ++k) {
-      const bool c = fr >= upc;
-      fr -= c ? upc : 0;
-      fj += c ? 1 : 0;
+      for (int k = 0; k < KG; ++k) {
+        const bool c = fr >= upc;
+        fr -= c ? upc : 0;
+        fj += c ? 1 : 0;
+      }
     }
     return d;
   };
@@ -748,26 +773,40 @@ __global__ __launch_bounds__(64 * QW * KG, 2) void kpw_kernel(KpfParams P, const
   };
   // LDS byte address of lds[0]
   const int lds0 = static_cast<int>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lds));
-  const int row0 = w * RPI + lane / NG;  // this lane's row in the wavefront's first load
+  // this lane's row and (placed) granule in a load; the load's first row is scalar
   constexpr int NGO = QW >= 4 ? 1 : 4 / QW;  // loads of different swizzle
   int goff[NGO];
 #pragma unroll
-  for (int n = 0; n < NGO; ++n) {
-    const int r = row0 + n * QW * RPI;
-    goff[n] = row0 * (D * 2) + (((lane % NG) ^ swz(r)) * 16);
-  }
+  for (int n = 0; n < NGO; ++n)
+    goff[n] = (lane / NG) * (D * 2) + (((lane % NG) ^ swz((w + QW * n) * RPI + lane / NG)) * 16);
+  static_assert(CC % RPI == 0, "a load's rows are of one chunk");
   auto issue = [&](const _Float16* pool, int tile, const Unit& d) {
-    int rows;
-    asm("s_max_i32 %0, %1, 0" : "=s"(rows) : "s"(d.len) : "scc");
-    const uint64_t p = reinterpret_cast<uint64_t>(pool + d.off);
-    const u32x4 rs = {static_cast<uint32_t>(p), static_cast<uint32_t>(p >> 32) & 0xffffu,
-                      static_cast<uint32_t>(rows * D * 2), static_cast<uint32_t>(kRsrcWord3)};
 #pragma unroll
-    for (int n = 0; n < LPT; ++n)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+    for (int n = 0; n < LPT; ++n) {
+      const int r0 = (w + QW * n) * RPI;  // first row of the load (uniform)
+      int64_t off = d.off[0];
+      int len = CC > 0 ? d.clen[0] : d.len, first = r0;
+      if constexpr (CC > 0) {
+        const int q = r0 / CC;
+        first = r0 % CC;
+#pragma unroll
+        for (int k = 1; k < G; ++k) {
+          off = q == k ? d.off[k] : off;
+          len = q == k ? d.clen[k] : len;
+        }
+      }
+      int rows;
+      asm("s_max_i32 %0, %1, 0" : "=s"(rows) : "s"(__builtin_amdgcn_readfirstlane(len)) : "scc");
+      const uint64_t p = reinterpret_cast<uint64_t>(pool + off);
+      const u32x4 rs = {static_cast<uint32_t>(p), static_cast<uint32_t>(p >> 32) & 0xffffu,
+                        static_cast<uint32_t>(rows * D * 2), static_cast<uint32_t>(kRsrcWord3)};
+      // one wait state between the m0 write and the load that reads it, five after
+      // a vector write of a scalar it reads (the compiler does not look inside)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                    :
-                   : "s"(lds0 + tile + (w + QW * n) * 1024), "v"(goff[n % NGO]), "s"(rs), "s"(n * QW * 1024)
+                   : "s"(lds0 + tile + r0 * (D * 2)), "v"(goff[n % NGO]), "s"(rs), "s"(first * (D * 2))
                    : "m0", "memory");
+    }
   };
   auto issue_k = [&](const Unit& d, int b) { issue(kbase, tile_k(b), d); };
   auto issue_v = [&](const Unit& d, int b) { issue(vbase, tile_v(b), d); };
@@ -822,6 +861,19 @@ __global__ __launch_bounds__(64 * QW * KG, 2) void kpw_kernel(KpfParams P, const
   // only for units that have such tokens (uniform), with their maximum again
   auto mask = [&](floatx16 (&sa)[JT], const Unit& d) {
     if (d.len >= TOK && d.pos + TOK - 1 <= pos_first) return;
+    if (CC > 0 && d.len < 0) {  // a short chunk inside the unit: chunk by chunk
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          constexpr int C1 = CC > 0 ? CC : 1;
+          const int t = 32 * jt + 8 * (r >> 2), q = t / C1 % G;
+          const int x = min(d.clen[q] - 1, pos - d.cpos[q]) - 4 * hl - (t % C1 + (r & 3));
+          sa[jt][r] = fminf(sa[jt][r], __int_as_float((x & INT32_MIN) | 0x7f800000));
+        }
+      rowmax(sa);
+      return;
+    }
     // min with +inf for a visible token, -inf for another: three vector ops
     // per element and no lane masks (32 of them spill the scalar registers)
     const int last = min(d.len - 1, pos - d.pos) - 4 * hl;  // last visible token of the unit
@@ -1011,8 +1063,8 @@ __global__ __launch_bounds__(64 * QW * KG, 2) void kpw_kernel(KpfParams P, const
     }
 }
 
-template <int D, int QW, int KG, int TOK>
-void launch_wide(const KpfParams& P, const PrefillArgs& a, hipStream_t stream) {
+template <int D, int QW, int KG, int TOK, int CC>
+void launch_wide_cc(const KpfParams& P, const PrefillArgs& a, hipStream_t stream) {
   constexpr int kLaneChunks = 64;
   const int blocks = (a.n_q + 32 * QW - 1) / (32 * QW) * a.H;
   const dim3 grid(8 * ((blocks + 7) / 8)), block(64 * QW * KG);  // a multiple of the XCD count
@@ -1020,16 +1072,23 @@ void launch_wide(const KpfParams& P, const PrefillArgs& a, hipStream_t stream) {
     KpfPath<kLaneChunks> path;
     for (int j = 0; j < a.n_chunks; ++j) path.slot[j] = a.host_path[j];
     for (int j = 0; j <= a.n_chunks; ++j) path.start[j] = a.host_path[a.n_chunks + j];
-    kpw_kernel<D, QW, KG, TOK, kLaneChunks><<<grid, block, 0, stream>>>(P, nullptr, nullptr, path);
+    kpw_kernel<D, QW, KG, TOK, CC, kLaneChunks><<<grid, block, 0, stream>>>(P, nullptr, nullptr, path);
   } else if (a.host_path) {
     KpfPath<kPrefillInlineChunks> path;
     for (int j = 0; j < a.n_chunks; ++j) path.slot[j] = a.host_path[j];
     for (int j = 0; j <= a.n_chunks; ++j) path.start[j] = a.host_path[a.n_chunks + j];
-    kpw_kernel<D, QW, KG, TOK, kPrefillInlineChunks><<<grid, block, 0, stream>>>(P, nullptr, nullptr, path);
+    kpw_kernel<D, QW, KG, TOK, CC, kPrefillInlineChunks><<<grid, block, 0, stream>>>(P, nullptr, nullptr, path);
   } else {
     const KpfPath<1> none{};
-    kpw_kernel<D, QW, KG, TOK, 0><<<grid, block, 0, stream>>>(P, a.chunk_slot, a.chunk_start, none);
+    kpw_kernel<D, QW, KG, TOK, CC, 0><<<grid, block, 0, stream>>>(P, a.chunk_slot, a.chunk_start, none);
   }
+}
+
+template <int D, int QW, int KG, int TOK>
+void launch_wide(const KpfParams& P, const PrefillArgs& a, hipStream_t stream) {
+  if (a.C == 16) launch_wide_cc<D, QW, KG, TOK, 16>(P, a, stream);
+  else if (TOK == 64 && a.C == 32) launch_wide_cc<D, QW, KG, TOK, TOK == 64 ? 32 : 0>(P, a, stream);
+  else launch_wide_cc<D, QW, KG, TOK, 0>(P, a, stream);
 }
 
 }  // namespace

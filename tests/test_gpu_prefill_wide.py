@@ -29,6 +29,12 @@ pytestmark = pytest.mark.gpu
     (7, 128, 130, 400, 70, "split"),           # 64-query tiles past one window
     (2, 64, 128, 460, 90, "interleaved"),      # 275 chunks, 64-query tiles
     (200, 128, 128, 30, 100, "split"),         # 64-query tiles, seven 32-row units a chunk
+    (32, 128, 128, 70, 150, "interleaved"),    # two chunks a unit, one short inside
+    (32, 64, 128, 70, 100, "split"),           # one 32-token chunk a 32-row unit
+    (16, 128, 128, 1100, 130, "split"),        # four chunks a unit, past one window
+    (16, 64, 256, 21, 90, "split"),
+    (16, 128, 128, 5, 100, "interleaved"),     # two chunks a unit, the first short
+    (16, 128, 256, 0, 3, "split"),             # one chunk in all
     (64, 128, 32, 1030, 130, "interleaved"),   # 16-query blocks: two parts, one round
     (64, 128, 32, 4000, 300, "split"),         # three parts, two rounds
     (16, 128, 32, 500, 257, "interleaved"),    # small chunks: 64-query tiles from half the chip on

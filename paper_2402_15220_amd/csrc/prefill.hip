@@ -577,10 +577,6 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef float float2_t __attribute__((ext_vector_type(2)));
-
 // Large joins: tiles of 32 * QW queries, QW wavefronts per key group, KG
 // groups that take alternate units, and the same online softmax as above, on
 // the 32x32x16 op (a wavefront owns 32 queries, so each K or V fragment read
@@ -800,6 +796,8 @@ __global__ __launch_bounds__(64 * QW * KG, 2) void kpw_kernel(KpfParams P, const
       const uint64_t p = reinterpret_cast<uint64_t>(pool + off);
       const u32x4 rs = {static_cast<uint32_t>(p), static_cast<uint32_t>(p >> 32) & 0xffffu,
                         static_cast<uint32_t>(rows * D * 2), static_cast<uint32_t>(kRsrcWord3)};
+      // rows past the chunk's length read as zeros: the range check counts the
+      // scalar offset too;
       // one wait state between the m0 write and the load that reads it, five after
       // a vector write of a scalar it reads (the compiler does not look inside)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"

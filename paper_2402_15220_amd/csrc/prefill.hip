@@ -683,6 +683,9 @@ __global__ __launch_bounds__(64 * QW * KG, 2) void kpw_kernel(KpfParams P, const
   // A window of 64 chunks of the path, one per lane: offset of the chunk's
   // rows in a head's pool (elements), first position and end. A unit's
   // descriptor is read from it with v_readlane (no memory wait in the loop).
+  // Lanes past the path hold a position that no query reaches (paths end below
+  // 2^30) and from which the mask below can subtract without wrapping.
+  constexpr int kNoPos = 0x60000000;
   const int nc = P.n_chunks;
   int win = 0, w_start = 0, w_end = 0;
   int64_t w_off = 0;
@@ -691,8 +694,8 @@ __global__ __launch_bounds__(64 * QW * KG, 2) void kpw_kernel(KpfParams P, const
     const int j = 64 * wi + lane;
     const bool in = j < nc;
     w_off = static_cast<int64_t>(chunk_slot(in ? j : 0)) * P.ss;
-    w_start = in ? chunk_start(j) : 0x7fffffff;
-    w_end = in ? chunk_start(j + 1) : 0x7fffffff;
+    w_start = in ? chunk_start(j) : kNoPos;
+    w_end = in ? chunk_start(j + 1) : kNoPos;
     // wait here, not where the loop reads them (that wait would also cover
     // the rows requested for later steps)
     asm volatile("" : "+v"(w_start), "+v"(w_end), "+v"(w_off));

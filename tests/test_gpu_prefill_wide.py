@@ -86,3 +86,23 @@ def test_moving_reference_maximum():
     err = np.abs(o[rows].astype(np.float64) - ref)
     print(f"[parity] spikes max_abs={err.max():.3e}", flush=True)
     assert (err <= 2e-3 + 2.0 ** -10 * np.abs(ref)).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,c", [(256, 16), (128, 16), (256, 32)])  # 128-query tiles, 64-query tiles
+@pytest.mark.parametrize("prefix,n_q", [(5, 3), (5, 8), (1, 10), (5, 16), (13, 16), (13, 30), (1, 40), (31, 9)])
+def test_units_that_end_past_the_path(c, H, d, prefix, n_q):
+    """A short first chunk, one or two more, and places of the unit past the
+    path's end: those hold no token for any query, the earliest positions
+    included. Every query is compared."""
+    print(f"[case] prefill wide short path c={c} H={H} d={d} prefix={prefix} n_q={n_q}", flush=True)
+    p = Pair(c, H, d, np.float16, 16)
+    pre = np.arange(prefix, dtype=np.int32)
+    for sid, tail in ((0, np.full(2, 90)), (1, 100 + np.arange(n_q))):
+        toks = np.concatenate([pre, tail]).astype(np.int32)
+        k, v = prefix_keyed_kv(7, toks, 0, H, d, np.float16)
+        p.insert(sid, toks, k, v)
+    for n in (n_q, prefix + n_q):  # the new tokens; the whole path from position 0
+        q = np.random.default_rng(n).standard_normal((n, H, d)).astype(np.float16)
+        o = p.cache.prefill(1, to_dev(q)).cpu().numpy()
+        assert_close(o, prefill_attention(p.tree, 1, q, 1.0 / np.sqrt(d)), np.float16, f"n={n}")

@@ -636,6 +636,7 @@ static ca_status launch_attention_call(ca_cache* cache, const void* q, void* o, 
   a.qscale = sc * 1.4426950408889634f;
   a.cnt = cnt;
   a.cnt_layout = ca::counter_layout(static_cast<size_t>(cache->tree.num_seqs()), a.H);
+  a.num_cus = cache->num_cus;
   a.row_map = row_map;
   hipError_t e = ca::launch_attention(a, cache->dw, s, cache->phase_mask, cache->side);
   if (e != hipSuccess) return hip_fail(e, "ca_attention launch");

@@ -1474,7 +1474,7 @@ constexpr int tpp_lds_bytes() {
 // Resident blocks per compute unit. The fp32 chunk-first path at d = 128
 // holds 32 registers each of K, V, q and O^T; capped at 128 for four blocks it
 // spills 63 of them. Three blocks still have twice the fp16 block's bytes in
-// flight each.
+// flight each (what it costs calls without chunk-first work, see launch_phases).
 template <typename T, int D>
 constexpr int tpp_blocks_per_cu() {
   return sizeof(T) == 4 && D == 128 ? 3 : 4;
@@ -1536,8 +1536,9 @@ __global__ __launch_bounds__(256 * kDeepChains) void kcf_deep_kernel(KcfParams P
     kcf_f32_block<D, 1, float, kDeepChains>(P, rest / zb, rest % zb, h, lds);
 }
 
+// (fp32, d = 128 is capped for the four blocks the fused kernel has no room for)
 template <typename T, int D, bool SM>
-__global__ __launch_bounds__(256) void ksf_kernel(KsfParams P) {
+__global__ __launch_bounds__(256, (tpp_blocks_per_cu<T, D>() < 4 ? 4 : 1)) void ksf_kernel(KsfParams P) {
   __shared__ __attribute__((aligned(16))) char lds[ksf_lds_bytes<T, D>()];
   const int b = static_cast<int>(blockIdx.x);
   ksf_block<T, D, SM>(P, b / P.H, b % P.H, lds);
@@ -1545,7 +1546,7 @@ __global__ __launch_bounds__(256) void ksf_kernel(KsfParams P) {
 
 template <typename T, int D, int NRT, bool SM>
 hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, hipStream_t s,
-                         const SideStream& side, const int32_t* group_ptr, int n_groups) {
+                         const SideStream& side, const int32_t* group_ptr, int n_groups, int num_cus) {
   const bool both = (mask & 3) == 3;
   if ((schedule == 1 || schedule == 2) && both) {
     // the fused launch always takes 16-row chunk-first blocks
@@ -1553,6 +1554,19 @@ hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, h
       if (n_sf == 0) {  // chunk-first work alone
         if (P.n_cf > 0) kcf_deep_kernel<T, D><<<P.n_cf, 256 * kDeepChains, 0, s>>>(P.cf, P.zb);
         return hipSuccess;
+      }
+      // Sequence-first work alone, where the fused kernel's registers cost it a
+      // place per compute unit: up to two rounds of four blocks go to the
+      // kernel of their own (32 heads, fp32, d = 128, fused / own: 32 rows of 64
+      // tokens 12.4 / 12.1 us, 64 of 64 22.4 / 21.7, 33 of 10 to 100 17.2 /
+      // 16.5). More rounds, and steps gathered from small chunks, stream as well
+      // or better with three (128 rows of 256 158.2 / 159.7, of 64 40.3 / 40.9; 32
+      // of 512 in 16-token chunks 78.9 / 79.9).
+      if constexpr (tpp_blocks_per_cu<T, D>() < 4 && !SM) {
+        if (P.n_cf == 0 && n_sf <= 8 * num_cus) {
+          ksf_kernel<T, D, SM><<<n_sf, 256, 0, s>>>(P.sf);
+          return hipSuccess;
+        }
       }
       const int grid = P.n_cf + n_sf;
       if (grid > 0) tpp_kernel<T, D, NRT, SM><<<grid, 256, 0, s>>>(P);
@@ -1624,8 +1638,8 @@ hipError_t launch_all(const AttnArgs& a, const DevWork& w, hipStream_t s, int ma
   P.n_cf = w.n_segs * P.zb * a.H;
   const int n_sf = w.n_items * a.H;
   hipError_t e;
-  if (nrt == 1) e = launch_phases<T, D, 1, SM>(P, n_sf, w.schedule, mask, s, side, w.seg_group_ptr, w.n_seg_groups);
-  else e = launch_phases<T, D, 2, SM>(P, n_sf, w.schedule, mask, s, side, w.seg_group_ptr, w.n_seg_groups);
+  if (nrt == 1) e = launch_phases<T, D, 1, SM>(P, n_sf, w.schedule, mask, s, side, w.seg_group_ptr, w.n_seg_groups, a.num_cus);
+  else e = launch_phases<T, D, 2, SM>(P, n_sf, w.schedule, mask, s, side, w.seg_group_ptr, w.n_seg_groups, a.num_cus);
   if (e != hipSuccess) return e;
   // Partial-writing schedules finish their rows inside the kernels; the merge
   // epilogue runs in the sequential schedule (split rows) or on its own.

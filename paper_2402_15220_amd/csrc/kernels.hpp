@@ -53,6 +53,7 @@ struct AttnArgs {
   float qscale;  // softmax scale * log2(e)
   int32_t* cnt;  // [B][H] arrival counters, zero between launches
   int cnt_layout; // counter_layout(rows, H)
+  int num_cus;
   const int32_t* row_map = nullptr;  // [B] tree row -> row of q and o (null: tree order)
 };
 

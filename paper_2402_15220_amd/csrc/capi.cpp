@@ -164,12 +164,12 @@ struct ca_cache {
   int32_t* d_slot_len = nullptr;
   char* d_blob = nullptr;
   size_t d_blob_cap = 0;
-  int32_t* d_cnt = nullptr;  // [B][H] arrival counters of the partial-writing schedules
+  int32_t* d_cnt = nullptr;  // arrival counters of the partial-writing schedules (counter_layout)
   size_t d_cnt_cap = 0;
   int32_t prefill_split = 0;     // key-range parts of a prefill tile (0: automatic)
   float* d_pf_ws = nullptr;      // prefill partials of split tiles
   size_t d_pf_ws_cap = 0;
-  int32_t* d_pf_cnt = nullptr;   // prefill arrival counters, one per tile
+  int32_t* d_pf_cnt = nullptr;   // prefill arrival counters, one per tile (tile_counter_shift)
   size_t d_pf_cnt_cap = 0;
   PinnedStaging work_stage;     // kernel context uploads
   PinnedStaging prefill_stage;  // prefill paths
@@ -352,7 +352,9 @@ struct ca_cache {
   }
 
   // At least n arrival counters in *p. They are zeroed once when allocated;
-  // every launch leaves them at zero again.
+  // every launch leaves them at zero again. The first allocation holds what
+  // the spread layouts can take (256 KiB), so growing batches and joins do not
+  // come back for more, which would wait for the stream.
   static ca_status ensure_counters(int32_t** p, size_t* cap_, size_t n, hipStream_t stream) {
     if (n <= *cap_) return CA_OK;
     hipError_t e;
@@ -362,7 +364,7 @@ struct ca_cache {
       *p = nullptr;
       *cap_ = 0;
     }
-    const size_t cap = std::max<size_t>(n * 2, 1024);
+    const size_t cap = n <= ca::kScratchCounters ? ca::kScratchCounters : n * 2;
     if ((e = hipMalloc(reinterpret_cast<void**>(p), cap * sizeof(int32_t))) != hipSuccess)
       return hip_fail(e, "counter alloc");
     if ((e = ca::launch_fill_i32(*p, static_cast<int64_t>(cap), 0, stream)) != hipSuccess)

@@ -51,7 +51,7 @@ struct AttnArgs {
   float* ws_ml;  // [n_parts][H][2] (running max in log2 units, sum)
   uint32_t ws_o_bytes;  // bytes of the ws_o region (below 4 GiB)
   float qscale;  // softmax scale * log2(e)
-  int32_t* cnt;  // [B][H] arrival counters, zero between launches
+  int32_t* cnt;  // counter_entries(rows, H) arrival counters, zero between launches
   int cnt_layout; // counter_layout(rows, H)
   int num_cus;
   const int32_t* row_map = nullptr;  // [B] tree row -> row of q and o (null: tree order)

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from parity_util import Pair, assert_close
+from paper_2402_15220_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +37,51 @@ def test_counter_layouts(rows, H):
             if out is not None:
                 torch.cuda.synchronize()
                 assert_close(out.cpu().numpy()[some], ref, np.float16, "noalloc")
+
+
+def _waits(call):
+    """True if the call waits for work that is already on the stream."""
+    torch.cuda.synchronize()
+    end = torch.cuda.Event()
+    torch.cuda._sleep(400_000_000)  # over 0.1 s
+    end.record()
+    call()
+    done = end.query()
+    torch.cuda.synchronize()
+    return done
+
+
+def test_growing_batches_never_wait():
+    """Counters are allocated once: neither a batch that fills up from one row
+    nor joins of more tiles make a call wait for the stream."""
+    print("[case] counters of a growing batch", flush=True)
+    H, d, c = 32, 128, 64
+    p = Pair(c, H, d, np.float16, 200, oracle_kv=False)
+    n = 24 * c + 1
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    kv = torch.randn((2, n + 250, H, d), generator=gen, device="cuda", dtype=torch.float16)
+    q = torch.randn((250, H, d), generator=gen, device="cuda", dtype=torch.float16)
+    out = torch.empty_like(q)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    s = p.cache.stream()
+    waited, joins = [], []
+    for rows in range(1, 65):
+        p.cache.insert(rows, np.append(np.arange(96), 1000 + rows), kv[0, :97], kv[1, :97])
+        if rows & (rows - 1) and rows not in (3, 7, 15, 33):
+            continue
+        p.cache.prepare()
+        call = lambda: B.ca_attention(p.cache.h, q.data_ptr(), out.data_ptr(), 0.0, ws.data_ptr(), ws.numel(), s)
+        if rows == 1:
+            call()
+        elif _waits(call):
+            waited.append(rows)
+    # joins whose key range is split, 32, 64 and 96 tiles; the first also allocates the partials
+    for i, new in enumerate((37, 100, 150)):
+        toks = np.concatenate([np.arange(96), 5000 * (i + 1) + np.arange(n - 96 + new)])
+        p.cache.insert(100 + i, toks, kv[0, :n + new].contiguous(), kv[1, :n + new].contiguous())
+        call = lambda: B.ca_prefill_attention(p.cache.h, 100 + i, q.data_ptr(), out.data_ptr(), new, 0.0, s)
+        if i == 0:
+            call()
+        elif _waits(call):
+            joins.append(new)
+    assert not waited and not joins, f"rows {waited}, joins {joins}"

@@ -186,7 +186,9 @@ ca_status ca_num_seqs(const ca_cache* cache, int64_t* B);
 ca_status ca_seq_order(const ca_cache* cache, int64_t* seq_ids, int64_t cap);
 
 /* Bytes of device workspace ca_attention needs for the current tree
- * (partial results of Algorithm 1 plus split partials; 0 is possible). */
+ * (partial results of Algorithm 1 plus split partials; 0 is possible). A
+ * workspace too small only for the partials of the automatic split (see
+ * ca_set_tuning) is accepted by ca_attention, which then keeps rows whole. */
 ca_status ca_workspace_size(const ca_cache* cache, size_t* bytes);
 
 /* Decode attention for every live sequence (Section 3.2, Algorithms 1 and 2):

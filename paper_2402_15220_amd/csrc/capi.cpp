@@ -9,6 +9,7 @@
 #include <new>
 #include <string>
 #include <unordered_set>
+#include <utility>
 #include <vector>
 
 #include "../../include/chunkattn.h"
@@ -249,8 +250,24 @@ struct ca_cache {
   // default schedule; the others keep rows whole unless told otherwise.
   int32_t split_rule() const { return split_chunks < 0 && schedule != 2 ? 0 : split_chunks; }
 
-  size_t ws_bytes() const {
-    const size_t np = static_cast<size_t>(work.n_parts);
+  // Where the automatic split cut rows but the same lists with rows whole need
+  // at most `limit` workspace bytes, take those lists (the segments, and the
+  // partials of the shared chunks, stay).
+  bool keep_rows_whole(size_t limit) {
+    if (work.split_rows == 0 || split_chunks >= 0) return false;
+    ca::WorkLists whole;
+    ca::build_tables(tree, &tables);
+    ca::build_work(tree, tables, work.seg_chunks, 0, schedule != 0, cfg.num_heads, num_cus, &whole,
+                   schedule == 4, token_head_bytes());
+    if (ws_bytes(whole) > limit) return false;
+    work = std::move(whole);
+    dw_valid = false;
+    return true;
+  }
+
+  size_t ws_bytes() const { return ws_bytes(work); }
+  size_t ws_bytes(const ca::WorkLists& w) const {
+    const size_t np = static_cast<size_t>(w.n_parts);
     const size_t H = cfg.num_heads, D = cfg.head_dim;
     return align_up(np * H * D * 4, 256) + align_up(np * H * 2 * 4, 256);
   }
@@ -658,7 +675,9 @@ static ca_status attention_impl(ca_cache* cache, const void* q, void* o, float s
   hipStream_t s = static_cast<hipStream_t>(stream);
   cache->ensure_work();
   const size_t need = cache->ws_bytes();
-  if (cache->work.n_parts > 0 && (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) & 255)))
+  // what the caller gave: nothing where it is missing or misaligned
+  const size_t have = !ws || (reinterpret_cast<uintptr_t>(ws) & 255) ? 0 : ws_bytes;
+  if (need > have && !cache->keep_rows_whole(have))
     return fail(CA_ERR_WORKSPACE, "ca_attention: workspace missing, misaligned or smaller than " +
                                       std::to_string(need) + " bytes");
   if (!cache->dw_valid && (st = cache->upload(s)) != CA_OK) return st;

@@ -147,3 +147,57 @@ def test_cut_rows_against_the_oracle(c, H, d, dt, prompt, lens):
         for _ in range(steps // 2 if step < 2 else 0):  # growth patches the last pieces
             kv = rng.standard_normal((2, len(ids), H, d)).astype(dt)
             p.append(ids, [7] * len(ids), kv[0], kv[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prompt,rows", [(0, 1), (200, 3)])
+def test_workspace_without_the_split(prompt, rows):
+    """A workspace that holds the partials of whole rows (none at all without
+    shared chunks) is accepted however far the rows grow; a smaller one is
+    refused and changes nothing."""
+    print(f"[case] workspace without the split prompt={prompt} rows={rows}", flush=True)
+    c, H, d, own = 64, 2, 128, 600
+    rng = np.random.default_rng(prompt + rows)
+    p = Pair(c, H, d, np.float16, 80)
+    whole = _table_cache(c, H, d)
+    B.ca_set_tuning(whole, split_chunks=0)
+    kp = rng.standard_normal((2, prompt, H, d)).astype(np.float16)
+    for sid in range(rows):
+        kv = np.concatenate([kp, rng.standard_normal((2, own, H, d)).astype(np.float16)], axis=1)
+        toks = list(range(prompt)) + [10_000 * (sid + 1) + i for i in range(own)]
+        p.insert(sid, toks, kv[0], kv[1])
+        B.ca_insert(whole, sid, toks)
+    need = B.ca_workspace_size(whole)
+    B.ca_destroy(whole)
+    assert (need > 0) == (prompt > 0)
+    ws = torch.empty(max(need, 256), dtype=torch.uint8, device="cuda")
+    s = p.cache.stream()
+
+    def attend(size):
+        row_seq = p.cache.seq_order()
+        q = rng.standard_normal((rows, H, d)).astype(np.float16)
+        qd, o = torch.from_numpy(q).cuda(), torch.empty((rows, H, d), dtype=torch.float16, device="cuda")
+        B.ca_attention(p.cache.h, qd.data_ptr(), o.data_ptr(), 0.0, ws.data_ptr() if size else 0, size, s)
+        torch.cuda.synchronize()
+        assert_close(o.cpu().numpy(), p.reference(row_seq, q, 0.0), np.float16, f"ws={size}")
+
+    cut = B.ca_workspace_size(p.cache.h)
+    assert cut > need
+    if need:
+        with pytest.raises(B.ChunkAttnError) as ei:
+            attend(need - 1)
+        assert ei.value.status == B.CA_ERR_WORKSPACE
+        assert B.ca_workspace_size(p.cache.h) == cut
+    attend(need)
+    ids = list(range(rows))
+    for step in range(3 * c):
+        kv = rng.standard_normal((2, rows, H, d)).astype(np.float16)
+        p.append(ids, [7] * rows, kv[0], kv[1])
+        if step % 50 == 0 or step == 3 * c - 1:
+            attend(need)
+    p.remove(0)  # a structural change plans the split again
+    if rows > 1:
+        rows -= 1
+        assert B.ca_workspace_size(p.cache.h) > 0
+        ids = list(p.cache.seq_order())
+        attend(need)

@@ -428,6 +428,75 @@ bool patch_work(const ChunkTree& tree, WorkLists* w) {
   return true;
 }
 
+namespace {
+
+// A row's items in the order of its private list.
+std::vector<std::vector<SfItem>> items_by_row(const WorkLists& w) {
+  std::vector<std::vector<SfItem>> rows(w.part_ptr.size() - 1);
+  for (const SfItem& it : w.items) rows[it.row].push_back(it);
+  for (auto& r : rows)
+    std::stable_sort(r.begin(), r.end(), [](const SfItem& x, const SfItem& y) { return x.cb < y.cb; });
+  return rows;
+}
+
+// Lists of a partial-writing schedule on their own: every partial is written
+// once and folded once, by the row it belongs to. Empty when they hold, else
+// what does not.
+const char* check_lists(const WorkLists& w) {
+  const size_t B = w.part_ptr.size() - 1;
+  for (const SfItem& it : w.items)
+    if (it.row < 0 || static_cast<size_t>(it.row) >= B) return "item row";
+  // a row's partials: its segments', then its pieces' in order
+  std::vector<std::vector<int32_t>> segs(B), want(B);
+  std::vector<char> written(static_cast<size_t>(w.n_parts), 0);
+  auto writes = [&](int32_t p) {
+    if (p < 0 || p >= w.n_parts || written[p]) return false;
+    return written[p] = 1, true;
+  };
+  for (const CfSeg& sg : w.segs)
+    for (int32_t r = sg.row_begin; r < sg.row_end; ++r) {
+      segs[r].push_back(sg.part_base + r - sg.row_begin);
+      if (!writes(segs[r].back())) return "segment partials";
+    }
+  std::vector<char> merged(B, 0);
+  for (int32_t r : w.mg_rows) {
+    if (r < 0 || static_cast<size_t>(r) >= B || merged[r]) return "merged rows";
+    merged[r] = 1;
+  }
+  const auto rows = items_by_row(w);
+  int32_t at = 0;  // the rows' private lists follow each other, as do a row's pieces
+  for (size_t r = 0; r < B; ++r) {
+    std::sort(segs[r].begin(), segs[r].end());
+    for (const SfItem& it : rows[r]) {
+      if (it.cb != at || it.ce < it.cb) return "pieces of a row";
+      at = it.ce;
+      if (it.out_part >= 0) {
+        want[r].push_back(it.out_part);
+        if (!writes(it.out_part)) return "piece partials";
+      }
+    }
+    // a whole row without shared chunks is finished by its item, any other by
+    // the merge of all its partials
+    const bool direct = rows[r].size() == 1 && segs[r].empty();
+    if (merged[r] == direct || want[r].size() != (direct ? 0 : rows[r].size())) return "kind of a row's items";
+    const int32_t pb = w.part_ptr[r], pe = w.part_ptr[r + 1];
+    const size_t ns = segs[r].size();
+    if (pb < 0 || pe < pb || static_cast<size_t>(pe) > w.parts.size() || pe - pb != static_cast<int32_t>(ns + want[r].size()))
+      return "partial counts";
+    std::vector<int32_t> own(w.parts.begin() + pb, w.parts.begin() + pb + ns);
+    std::sort(own.begin(), own.end());
+    if (own != segs[r] || !std::equal(want[r].begin(), want[r].end(), w.parts.begin() + pb + ns))
+      return "partials of a row";
+  }
+  if (at != static_cast<int32_t>(w.priv_slot.size())) return "private list";
+  if (w.part_ptr.back() != static_cast<int32_t>(w.parts.size())) return "partial list";
+  for (char x : written)
+    if (!x) return "unwritten partials";
+  return "";
+}
+
+}  // namespace
+
 const char* same_work(const WorkLists& a, const WorkLists& b) {
   if (a.seg_slots != b.seg_slots || a.segs.size() != b.segs.size()) return "segments";
   for (size_t i = 0; i < a.segs.size(); ++i)
@@ -441,6 +510,20 @@ const char* same_work(const WorkLists& a, const WorkLists& b) {
         a.n_parts != b.n_parts)
       return "partial lists";
     if (a.items.size() != b.items.size()) return "item count";
+  }
+  if (cut) {
+    // Pieces may lie elsewhere and number the partials after them otherwise:
+    // each side is checked on its own, then what does not depend on them.
+    if (a.part_ptr.size() != b.part_ptr.size()) return "rows";
+    for (const WorkLists* w : {&a, &b})
+      if (const char* d = check_lists(*w); *d) return d;
+    auto folds = [](const WorkLists& w, size_t r) {  // the row's segment partials, in folding order
+      size_t pieces = 0;
+      for (const SfItem& it : w.items) pieces += it.row == static_cast<int32_t>(r) && it.out_part >= 0;
+      return std::vector<int32_t>(w.parts.begin() + w.part_ptr[r], w.parts.begin() + w.part_ptr[r + 1] - pieces);
+    };
+    for (size_t r = 0; r + 1 < a.part_ptr.size(); ++r)
+      if (folds(a, r) != folds(b, r)) return "segments of a row";
   }
   auto key = [cut](const WorkLists& w) {
     std::vector<std::vector<int32_t>> k(w.item_of_row.size());

@@ -99,8 +99,10 @@ bool patch_work(const ChunkTree& tree, WorkLists* w);
 // Compare two work lists up to the order of sequence-first items: every row
 // has the same private slots and item kind, segments and partial lists are
 // equal. Empty string when they agree, else what differs. Where the
-// automatic split cut a row in either list, the pieces (and so the partial
-// lists) may differ and only their concatenation is compared.
+// automatic split cut a row in either list, the pieces (and so the numbers of
+// the partials after them) may differ: then both lists are checked on their
+// own (every partial written once and folded once by its row, a row's pieces
+// tiling its private list) and the rows' slots and segment partials compared.
 const char* same_work(const WorkLists& a, const WorkLists& b);
 
 }  // namespace ca

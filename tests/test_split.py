@@ -2,6 +2,8 @@
 seen through the workspace size, decode growth on cut rows, and the results of
 cut rows against the oracle."""
 import os
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -76,6 +78,20 @@ def test_growth_patches_cut_rows(H, rows):
     assert st["patches"] > 550               # one per new chunk of every row, few rebuilds
     assert len(sizes) <= 4
     B.ca_destroy(h)
+
+
+def test_patch_check_finds_planted_mistakes(tmp_path):
+    """The comparison of a patched list with a rebuilt one, on lists with cut
+    rows: wrong, missing, doubled or misnumbered pieces and partials."""
+    if shutil.which("g++") is None:
+        pytest.skip("no g++ in this image")
+    here = os.path.dirname(os.path.abspath(__file__))
+    csrc = os.path.join(os.path.dirname(here), "paper_2402_15220_amd", "csrc")
+    exe = str(tmp_path / "check")
+    subprocess.run(["g++", "-std=c++17", "-O1", f"-I{csrc}", os.path.join(here, "work_lists_check.cpp"),
+                    os.path.join(csrc, "tables.cpp"), os.path.join(csrc, "tree.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout == "", r.stdout + r.stderr
 
 
 @pytest.mark.parametrize("H,parts", [(128, 248), (64, 249)])

@@ -877,18 +877,16 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
       }
     }
   }
-  // 32-query wavefronts wherever their tiles give every compute unit a block:
-  // 128-query tiles (each K/V element through the caches once per 128
-  // queries), else 64-query ones; smaller joins are latency-bound and keep the
-  // 16-query blocks and their key-range split. 32 heads, 16-query / 64 / 128-query
-  // blocks: 1,100 queries over 1,100 positions 38.2 / 25.9 / 27.2 us, 900 over
-  // 1,200 38.2 / 27.9 / 27.1, 512 over 1,536 24.9 / 24.8 / 31.0, 300 over 300
-  // 9.3 / 9.7 / 10.6, 200 over 1,224 16.9 / 20.4 / 25.4. Exactly a block per
-  // compute unit is a tie that long paths win (16-query / 64: 512 queries over
-  // 512 positions 11.7 / 12.4 us, 1,536 23.9 / 24.4, 3,000 41.9 / 41.8, 6,000
-  // 78.9 / 77.5; 16 heads, 1,024 over 1,024 17.4 / 18.1, 1,000 over 4,000 53.1 /
-  // 52.9). At d = 64 a 64-query tile has too little work per unit: 16 heads,
-  // 1,024 over 2,024 20.0 / 21.8 us.
+  // 32-query wavefronts where the 16-query blocks would need a second round:
+  // 128-query tiles where those give every compute unit a block (each K/V
+  // element through the caches once per 128 queries), else 64-query ones. Up to
+  // a block per compute unit the 16-query blocks and their key-range split
+  // stay. 32 heads, 16-query / 64 / 128-query blocks: 1,100 queries over 1,100
+  // positions 36.4 / 26.0 / 27.0 us, 900 over 1,200 37.8 / 27.5 / 26.6, 576 over
+  // 4,000 97.7 / 67.1 / 67.0, 513 over 1,536 40.8 / 28.3 / 29.8; 512 over 1,536
+  // 24.7 / 25.0 / 29.8, over 512 11.5 / 12.3 / 14.1, over 6,000 82.0 / 80.0 / 98.5;
+  // 300 over 300 9.0 / 9.5 / 10.3. At d = 64 a 64-query tile has too little work
+  // per unit: 16 heads, 1,024 over 2,024 20.4 / 22.5 us.
   // Over chunks of at most 32 tokens the 64-query tiles go wherever they are
   // the faster by the same kind of model (two blocks a compute unit, ~0.87 us
   // per pair of 32-row units, which hold two 16-token chunks; 300 queries over
@@ -899,7 +897,7 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
     const double us64 = (tiles + 2 * cus - 1) / (2 * cus) * (5.0 + 0.87 * ((units32 + 1) / 2));
     if ((n_q + 127) / 128 * a.H >= cus) a.tile_rows = 128;
     else if (a.C <= 32 ? cache->prefill_split == 0 && us64 < best_us
-                       : a.D == 128 && (tiles > cus || (tiles == cus && pos >= 3000)))
+                       : a.D == 128 && tiles > cus)
       a.tile_rows = 64;
     if (a.tile_rows > 0) split = 1;
   }

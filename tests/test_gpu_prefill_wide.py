@@ -15,8 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 # heads x ceil(n_q / 128) >= 256 blocks: 128-query tiles; else, if heads x
-# ceil(n_q / 64) > 256, or 256 over at least 3,000 positions, 64-query tiles
-# (256 compute units); over chunks of at most 32 tokens a model decides
+# ceil(n_q / 64) > 256, 64-query tiles (256 compute units); over chunks of at
+# most 32 tokens a model decides
 @pytest.mark.parametrize("c,d,H,prefix,n_q,layout", [
     (64, 128, 128, 100, 129, "interleaved"),   # 128-query tiles, the last of one query
     (64, 64, 256, 0, 77, "split"),             # one 128-query tile, nothing cached
@@ -25,9 +25,10 @@ pytestmark = pytest.mark.gpu
     (3, 128, 128, 50, 250, "interleaved"),     # 100 chunks: past one window
     (1, 64, 256, 200, 100, "split"),           # 300 chunks: device table
     (64, 128, 130, 100, 65, "split"),          # 64-query tiles, two key groups
-    (64, 128, 128, 100, 65, "split"),          # 256 64-query tiles, a short path: 16-query blocks
-    (64, 128, 32, 2480, 512, "interleaved"),   # the same, 2,992 positions
-    (64, 128, 32, 2488, 512, "split"),         # 3,000: 64-query tiles
+    (64, 128, 128, 100, 65, "split"),          # 256 64-query tiles: 16-query blocks
+    (64, 128, 32, 2480, 512, "interleaved"),   # the same over a longer path
+    (64, 128, 32, 2488, 512, "split"),
+    (64, 128, 32, 2487, 513, "split"),         # 288: 64-query tiles
     (16, 64, 128, 1, 128, "interleaved"),      # 64-query tiles, 32-row units
     (100, 128, 256, 5, 20, "interleaved"),     # 128-query tile, mostly past n_q
     (7, 128, 130, 400, 70, "split"),           # 64-query tiles past one window

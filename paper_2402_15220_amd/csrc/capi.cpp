@@ -891,12 +891,15 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
   // the faster by the same kind of model (two blocks a compute unit, ~0.87 us
   // per pair of 32-row units, which hold two 16-token chunks; 300 queries over
   // 1,300 positions in 16-token chunks: 80 us in one part of 16-query blocks,
-  // 65 in three, 23 so).
+  // 65 in three, 23 so), but not for one or two chunks, which a 16-query block
+  // takes in one pair (2 heads, 16 queries over 16 positions in 16-token chunks 4.7
+  // us in 16-query blocks / 5.5 in 64-query tiles, 32 over 32 5.6 / 5.9, 48 over 48
+  // 7.3 / 6.3).
   if (cache->prefill_split <= 1) {
     const int64_t units32 = a.C == 16 ? (nc + 1) / 2 : static_cast<int64_t>(nc) * ((a.C + 31) / 32);
     const double us64 = (tiles + 2 * cus - 1) / (2 * cus) * (5.0 + 0.87 * ((units32 + 1) / 2));
     if ((n_q + 127) / 128 * a.H >= cus) a.tile_rows = 128;
-    else if (a.C <= 32 ? cache->prefill_split == 0 && us64 < best_us
+    else if (a.C <= 32 ? cache->prefill_split == 0 && nc > 2 && us64 < best_us
                        : a.D == 128 && tiles > cus)
       a.tile_rows = 64;
     if (a.tile_rows > 0) split = 1;

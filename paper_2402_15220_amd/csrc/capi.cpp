@@ -885,8 +885,19 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
   // positions 36.4 / 26.0 / 27.0 us, 900 over 1,200 37.8 / 27.5 / 26.6, 576 over
   // 4,000 97.7 / 67.1 / 67.0, 513 over 1,536 40.8 / 28.3 / 29.8; 512 over 1,536
   // 24.7 / 25.0 / 29.8, over 512 11.5 / 12.3 / 14.1, over 6,000 82.0 / 80.0 / 98.5;
-  // 300 over 300 9.0 / 9.5 / 10.3. At d = 64 a 64-query tile has too little work
-  // per unit: 16 heads, 1,024 over 2,024 20.4 / 22.5 us.
+  // 300 over 300 9.0 / 9.5 / 10.3.
+  // At d = 64 a tile has half the work per unit. Up to 128-query tiles for every
+  // compute unit the 16-query blocks stay (16 heads, 1,024 over 2,024 20.4 / 22.5
+  // us); above, 128-query tiles pay where they come in rounds enough to even out
+  // (8,155 over 8,155 248 / 203 / 194, 32 heads, 4,059 over 4,059 137 in 16-query,
+  // 110 in 128-query tiles) or are of like lengths, behind a cached prefix (32
+  // heads, 2,011 over 6,033 154 / 133 / 125; but 987 over 2,961, 256 tiles, 42 /
+  // 41 / 40); else their longest tile sets the time and 64-query ones do better
+  // (10 heads, 3,400 over 3,400 43.5 / 43.7 / 58.7, 8 heads, 4,059 over 4,059 45.9
+  // in 16-query, 51.2 in 128-query tiles). Chunks of 33 to 63 tokens leave the
+  // 128-query tiles' 64-row units part masked, and few tiles lose to the 16-query
+  // blocks either way (48-token chunks, 32 heads, 1,499 over 1,499 48.9 / 39.2 /
+  // 53.2, 987 over 987 25.8 / 27.9 / 26.8).
   // Over chunks of at most 32 tokens the 64-query tiles go wherever they are
   // the faster by the same kind of model (two blocks a compute unit, ~0.87 us
   // per pair of 32-row units, which hold two 16-token chunks; 300 queries over
@@ -898,9 +909,14 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
   if (cache->prefill_split <= 1) {
     const int64_t units32 = a.C == 16 ? (nc + 1) / 2 : static_cast<int64_t>(nc) * ((a.C + 31) / 32);
     const double us64 = (tiles + 2 * cus - 1) / (2 * cus) * (5.0 + 0.87 * ((units32 + 1) / 2));
-    if ((n_q + 127) / 128 * a.H >= cus) a.tile_rows = 128;
+    const int64_t tiles128 = (n_q + 127) / 128 * a.H;
+    // d = 64: rounds enough, or at least 2/7 of the path cached; units filled
+    const bool even = tiles128 >= 3 * cus || (4 * tiles128 >= 7 * cus && 7 * (L - n_q) >= 2 * L);
+    const bool filled = a.C >= 64 || a.C == 32 || a.C == 16;
+    if (tiles128 >= cus && (a.D == 128 || (even && filled))) a.tile_rows = 128;
     else if (a.C <= 32 ? cache->prefill_split == 0 && nc > 2 && us64 < best_us
-                       : a.D == 128 && tiles > cus)
+             : a.D == 128 ? tiles > cus
+                          : tiles128 >= cus && (filled || 2 * tiles128 >= 3 * cus))
       a.tile_rows = 64;
     if (a.tile_rows > 0) split = 1;
   }

@@ -14,14 +14,23 @@ from workloads import prefix_keyed_kv
 pytestmark = pytest.mark.gpu
 
 
-# heads x ceil(n_q / 128) >= 256 blocks: 128-query tiles; else, if heads x
-# ceil(n_q / 64) > 256, 64-query tiles (256 compute units); over chunks of at
-# most 32 tokens a model decides
+# heads x ceil(n_q / 128) >= 256 blocks (compute units): 128-query tiles, at
+# d = 64 only in three rounds or, from 448 blocks on, with 2/7 of the path cached,
+# and not in chunks that part fill the units; else, if heads x ceil(n_q / 64) >
+# 256 (d = 64: where the 128-query tiles were in question), 64-query tiles; over
+# chunks of at most 32 tokens a model decides
 @pytest.mark.parametrize("c,d,H,prefix,n_q,layout", [
     (64, 128, 128, 100, 129, "interleaved"),   # 128-query tiles, the last of one query
-    (64, 64, 256, 0, 77, "split"),             # one 128-query tile, nothing cached
+    (64, 64, 256, 0, 77, "split"),             # nothing cached: 64-query tiles
+    (64, 64, 256, 0, 300, "interleaved"),      # 768 128-query tiles
+    (64, 64, 256, 120, 200, "split"),          # 512, 3/8 cached
+    (16, 64, 256, 100, 200, "interleaved"),    # four chunks a unit, d = 64
+    (32, 64, 256, 100, 200, "split"),          # two
+    (48, 64, 256, 120, 200, "split"),          # units part masked: 64-query tiles
+    (48, 64, 256, 30, 70, "interleaved"),      # the same, 256: 16-query blocks
     (16, 128, 128, 37, 200, "interleaved"),    # a short chunk mid-path
-    (130, 64, 128, 300, 140, "split"),         # three units a chunk, the last of two rows
+    (130, 64, 128, 300, 140, "split"),         # five 32-row units a chunk, the last of two rows
+    (130, 128, 128, 300, 140, "split"),        # three 64-row units a chunk, the last of two rows
     (3, 128, 128, 50, 250, "interleaved"),     # 100 chunks: past one window
     (1, 64, 256, 200, 100, "split"),           # 300 chunks: device table
     (64, 128, 130, 100, 65, "split"),          # 64-query tiles, two key groups
@@ -90,7 +99,8 @@ def test_moving_reference_maximum():
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("H,c", [(256, 16), (128, 16), (256, 32)])  # 128-query tiles, 64-query tiles
+# 128-query tiles (d = 64: of 768 heads), 64-query tiles or 16-query blocks, 128-query tiles
+@pytest.mark.parametrize("H,c", [(256, 16), (768, 16), (128, 16), (256, 32)])
 @pytest.mark.parametrize("prefix,n_q", [(5, 3), (5, 8), (1, 10), (5, 16), (13, 16), (13, 30), (1, 40), (31, 9)])
 def test_units_that_end_past_the_path(c, H, d, prefix, n_q):
     """A short first chunk, one or two more, and places of the unit past the

@@ -265,8 +265,8 @@ struct KsfParams {
   int C;
   float qscale;
   int32_t* cnt;  // partial-writing schedules: per (row, head) arrival counters, else null
-  int cnt_layout;  // see counter_layout()
   const int32_t* row_map;  // tree row -> row of q and o (null: tree order)
+  int cnt_layout;  // see counter_layout()
 };
 
 // Lane layout: a token row of d elements is read by LPT = d/EPL lanes, 16
@@ -630,13 +630,22 @@ struct KcfParams {
   // partial-writing schedules only (null otherwise): per (row, head) arrival counters
   // and what the last contributor needs to finish the row
   int32_t* cnt;
-  int cnt_layout;
   void* o;
   const int32_t* part_ptr;
   const int32_t* parts;
   const int32_t* row_map;  // tree row -> row of q and o (null: tree order)
-  int seg_base = 0;        // index in the whole segment list of segs[0]
+  int seg_base;            // index in the whole segment list of segs[0]
+  int cnt_layout;          // see counter_layout()
 };
+
+// The block index, after the arguments a chunk-first block reads first: left to
+// the compiler, their load waits behind the divisions that take the index
+// apart, which a short call sees as 0.2 us.
+__device__ __forceinline__ int block_index(const KcfParams& P) {
+  int b = static_cast<int>(blockIdx.x);
+  asm("" : "+s"(b) : "s"(P.slot_len), "s"(P.segs), "s"(P.seg_slots));
+  return b;
+}
 
 // Partial-writing schedules: after a chunk-first block wrote its partials for
 // rows [rb, rb+nrows), count its arrival on each row; the rows for which it
@@ -873,7 +882,9 @@ __device__ __forceinline__ void cf_publish(const KcfParams& P, const CfSeg& sg, 
 // takes 16 tokens, so chunks of up to 16 tokens go one to a wavefront, of up
 // to 32 one to a pair; with longer ones the four share each chunk. (One
 // 16-token chunk per chain left three of four wavefronts idle: 32 identical
-// sequences of 2,048 tokens took 21 us so, 12.4 us now.)
+// sequences of 2,048 tokens took 21 us so, 12.4 us now.) Kernels for longer
+// chunks (SM false) have the 1 as a constant: with a count known only at run
+// time their chains took 5% longer (two rows over 4,771 tokens, 2 heads).
 __device__ __forceinline__ int chunks_at_once(int C) { return C <= 16 ? 4 : C <= 32 ? 2 : 1; }
 
 // Lazy reference maximum of the chunk-first softmax (log2 units): P <= 2^8.
@@ -908,7 +919,7 @@ constexpr int kcf_f16_lds_bytes() {
 //     one half-wavefront reads fall in disjoint banks).
 // No barrier inside the chunk loop; the four wavefront states are merged
 // once at the end of the segment.
-template <int D, int NRT, typename OUT_T = _Float16, int NCH = 1>
+template <bool SM, int D, int NRT, typename OUT_T = _Float16, int NCH = 1>
 __device__ __forceinline__ void kcf_f16_block(const KcfParams& P, int seg, int z, int h, char* lds) {
   constexpr int KS = D / 32;      // 16x16x32 steps over d for S^T
   constexpr int DT = D / 16;      // 16-wide d tiles of O^T (every wavefront holds all)
@@ -925,7 +936,7 @@ __device__ __forceinline__ void kcf_f16_block(const KcfParams& P, int seg, int z
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // chain (wave-uniform): takes chunks chain, chain + stride, ...; wq: this
   // wavefront's 16-token slice of them
-  const int at_once = chunks_at_once(P.C), stride = NCH * at_once;
+  const int at_once = SM ? chunks_at_once(P.C) : 1, stride = NCH * at_once;
   const int wpc = 4 / at_once;
   const int chain = __builtin_amdgcn_readfirstlane((w >> 2) * at_once + (w & 3) / wpc);
   const int wq = (w & 3) % wpc;
@@ -1191,7 +1202,7 @@ constexpr int kcf_f32_lds_bytes() {
   return 4 * NCH * 16 * NRT * (D + 4) * 4 + 2 * 4 * NCH * 16 * NRT * 4;
 }
 
-template <int D, int NRT, typename OUT_T = float, int NCH = 1>
+template <bool SM, int D, int NRT, typename OUT_T = float, int NCH = 1>
 __device__ __forceinline__ void kcf_f32_block(const KcfParams& P, int seg, int z, int h, char* lds) {
   constexpr int KS = D / 16;      // 16-byte granules of a K row per lane
   constexpr int VC = D / 64;      // 16-byte granules of a V row per lane
@@ -1200,7 +1211,7 @@ __device__ __forceinline__ void kcf_f32_block(const KcfParams& P, int seg, int z
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // chain (wave-uniform): takes chunks chain, chain + stride, ...; wq: this
   // wavefront's 16-token slice of them
-  const int at_once = chunks_at_once(P.C), stride = NCH * at_once;
+  const int at_once = SM ? chunks_at_once(P.C) : 1, stride = NCH * at_once;
   const int wpc = 4 / at_once;
   const int chain = __builtin_amdgcn_readfirstlane((w >> 2) * at_once + (w & 3) / wpc);
   const int wq = (w & 3) % wpc;
@@ -1491,9 +1502,9 @@ __global__ __launch_bounds__(256, (tpp_blocks_per_cu<T, D>())) void tpp_kernel(T
     const int z = rest % P.zb;
     const int seg = rest / P.zb;
     if constexpr (sizeof(T) == 2)
-      kcf_f16_block<D, NRT>(P.cf, seg, z, h, lds);
+      kcf_f16_block<SM, D, NRT>(P.cf, seg, z, h, lds);
     else
-      kcf_f32_block<D, NRT>(P.cf, seg, z, h, lds);
+      kcf_f32_block<SM, D, NRT>(P.cf, seg, z, h, lds);
   } else {
     const int bb = b - P.n_cf;
     ksf_block<T, D, SM>(P.sf, bb / H, bb % H, lds);
@@ -1501,17 +1512,17 @@ __global__ __launch_bounds__(256, (tpp_blocks_per_cu<T, D>())) void tpp_kernel(T
 }
 
 // The phases as separate launches (same block functions, own resources).
-template <typename T, int D, int NRT>
+template <typename T, int D, int NRT, bool SM>
 __global__ __launch_bounds__(256) void kcf_kernel(KcfParams P, int zb) {
   constexpr int L = sizeof(T) == 2 ? kcf_f16_lds_bytes<D, NRT>() : kcf_f32_lds_bytes<D, NRT>();
   __shared__ __attribute__((aligned(16))) char lds[L];
-  const int b = static_cast<int>(blockIdx.x);
+  const int b = block_index(P);
   const int h = b % P.H;
   const int rest = b / P.H;
   if constexpr (sizeof(T) == 2)
-    kcf_f16_block<D, NRT>(P, rest / zb, rest % zb, h, lds);
+    kcf_f16_block<SM, D, NRT>(P, rest / zb, rest % zb, h, lds);
   else
-    kcf_f32_block<D, NRT>(P, rest / zb, rest % zb, h, lds);
+    kcf_f32_block<SM, D, NRT>(P, rest / zb, rest % zb, h, lds);
 }
 
 // Chunk-first work alone (no sequence-first item in the call, e.g. identical
@@ -1523,17 +1534,17 @@ __global__ __launch_bounds__(256) void kcf_kernel(KcfParams P, int zb) {
 // Table 3's all-shared cells against one chain with a two-deep prefetch
 // (same) and four chains (slower: more fixed cost per chain).
 constexpr int kDeepChains = 2;
-template <typename T, int D>
+template <typename T, int D, bool SM>
 __global__ __launch_bounds__(256 * kDeepChains) void kcf_deep_kernel(KcfParams P, int zb) {
   constexpr int L = sizeof(T) == 2 ? kcf_f16_lds_bytes<D, 1, kDeepChains>() : kcf_f32_lds_bytes<D, 1, kDeepChains>();
   __shared__ __attribute__((aligned(16))) char lds[L];
-  const int b = static_cast<int>(blockIdx.x);
+  const int b = block_index(P);
   const int h = b % P.H;
   const int rest = b / P.H;
   if constexpr (sizeof(T) == 2)
-    kcf_f16_block<D, 1, _Float16, kDeepChains>(P, rest / zb, rest % zb, h, lds);
+    kcf_f16_block<SM, D, 1, _Float16, kDeepChains>(P, rest / zb, rest % zb, h, lds);
   else
-    kcf_f32_block<D, 1, float, kDeepChains>(P, rest / zb, rest % zb, h, lds);
+    kcf_f32_block<SM, D, 1, float, kDeepChains>(P, rest / zb, rest % zb, h, lds);
 }
 
 // (fp32, d = 128 is capped for the four blocks the fused kernel has no room for)
@@ -1552,7 +1563,7 @@ hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, h
     // the fused launch always takes 16-row chunk-first blocks
     if constexpr (NRT == 1) {
       if (n_sf == 0) {  // chunk-first work alone
-        if (P.n_cf > 0) kcf_deep_kernel<T, D><<<P.n_cf, 256 * kDeepChains, 0, s>>>(P.cf, P.zb);
+        if (P.n_cf > 0) kcf_deep_kernel<T, D, SM><<<P.n_cf, 256 * kDeepChains, 0, s>>>(P.cf, P.zb);
         return hipSuccess;
       }
       // Sequence-first work alone, where the fused kernel's registers cost it a
@@ -1581,7 +1592,7 @@ hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, h
     hipError_t e;
     if ((e = hipEventRecord(side.fork, s)) != hipSuccess) return e;
     if ((e = hipStreamWaitEvent(side.stream, side.fork, 0)) != hipSuccess) return e;
-    kcf_kernel<T, D, NRT><<<P.n_cf, 256, 0, side.stream>>>(P.cf, P.zb);
+    kcf_kernel<T, D, NRT, SM><<<P.n_cf, 256, 0, side.stream>>>(P.cf, P.zb);
     if ((e = hipEventRecord(side.join, side.stream)) != hipSuccess) return e;
     ksf_kernel<T, D, SM><<<n_sf, 256, 0, s>>>(P.sf);
     return hipStreamWaitEvent(s, side.join, 0);
@@ -1604,11 +1615,11 @@ hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, h
         g.segs = cf.segs + group_ptr[gi];
         g.seg_base = group_ptr[gi];
         const int nb = (group_ptr[gi + 1] - group_ptr[gi]) * P.zb * cf.H;
-        if (nb > 0) kcf_kernel<T, D, NRT><<<nb, 256, 0, s>>>(g, P.zb);
+        if (nb > 0) kcf_kernel<T, D, NRT, SM><<<nb, 256, 0, s>>>(g, P.zb);
       }
     }
   } else if ((mask & 1) && P.n_cf > 0) {
-    kcf_kernel<T, D, NRT><<<P.n_cf, 256, 0, s>>>(cf, P.zb);
+    kcf_kernel<T, D, NRT, SM><<<P.n_cf, 256, 0, s>>>(cf, P.zb);
   }
   if ((mask & 2) && n_sf > 0) ksf_kernel<T, D, SM><<<n_sf, 256, 0, s>>>(sf);
   return hipSuccess;
@@ -1621,10 +1632,10 @@ hipError_t launch_all(const AttnArgs& a, const DevWork& w, hipStream_t s, int ma
   const bool counting = w.schedule == 2 || w.schedule == 3;  // the last contributor finishes each row
   P.cf = KcfParams{a.q, a.kpool, a.vpool, a.ss, a.hs, a.slot_len, w.segs, w.seg_slots, a.ws_o,
                    reinterpret_cast<float2*>(a.ws_ml), a.ws_o_bytes, a.H, a.C, a.qscale,
-                   counting ? a.cnt : nullptr, a.cnt_layout, a.o, w.part_ptr, w.parts, a.row_map};
+                   counting ? a.cnt : nullptr, a.o, w.part_ptr, w.parts, a.row_map, 0, a.cnt_layout};
   P.sf = KsfParams{a.q, a.o, a.kpool, a.vpool, a.ss, a.hs, a.slot_len, w.items, w.priv_slot, w.part_ptr,
                    w.parts, a.ws_o, reinterpret_cast<float2*>(a.ws_ml), a.ws_o_bytes, a.H, a.C,
-                   a.qscale, counting ? a.cnt : nullptr, a.cnt_layout, a.row_map};
+                   a.qscale, counting ? a.cnt : nullptr, a.row_map, a.cnt_layout};
   // At most 16 or 32 covered rows per chunk-first block; wider runs take
   // several row blocks, which re-read the chunk. Their block indices differ
   // by a multiple of H, so for H a multiple of 8 they land on the same XCD

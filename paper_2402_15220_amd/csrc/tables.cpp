@@ -137,7 +137,7 @@ void build_tables(const ChunkTree& tree, Tables* out) {
 
 void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int32_t split_chunks,
                 bool partial_items, int32_t num_heads, int32_t num_cus, WorkLists* out,
-                bool serial_reduce, int32_t token_head_bytes) {
+                bool serial_reduce, int32_t token_head_bytes, bool counted) {
   WorkLists& W = *out;
   if (serial_reduce) {
     // every segment is one more launch: by default a run is one segment
@@ -214,10 +214,19 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
     // than the shorter chains save (8 rows, one head, 64 shared chunks: 18.9
     // us in 64 segments, 12.8 in 32, 10.7 in 16, 11.2 in 8; 16 rows, 8 heads,
     // 32 shared chunks 10.6 in 32, 10.3 in 16, 11.5 in 8)
-    int64_t longest = 0;
-    for (const auto& chain : runs)
-      longest = std::max<int64_t>(longest, step_count(static_cast<int64_t>(chain.size())));
-    while (pow2 * 16 < longest && pow2 < 16) pow2 <<= 1;
+    // (in the schedules whose rows are finished inside the launch; 3 rows, one
+    // head, 32 shared chunks of 200 as launches of their own 10.9 in 32 segments,
+    // 12.4 in 16). A longer chain pays while its length squared, times what a
+    // step costs against 64 tokens of 512 bytes, is below ~0.8 of the run (3
+    // rows, one head, fp32, 80 chunks of 200: 23.8 in segments of one chunk, 21.8
+    // of two, 42.8 of eight; 100 chunks of 64: 23.6, of four 14.9, of eight 17.3).
+    if (counted) {
+      int64_t longest = 0;
+      for (const auto& chain : runs)
+        longest = std::max<int64_t>(longest, step_count(static_cast<int64_t>(chain.size())));
+      const int64_t cost = (static_cast<int64_t>(c) + 63) / 64 * std::max(1, token_head_bytes / 512);
+      while (pow2 * 16 < longest && pow2 < 16 && (cost == 1 || 5 * cost * pow2 * pow2 <= longest)) pow2 <<= 1;
+    }
     seg_chunks = static_cast<int32_t>(std::min<int64_t>(cap, pow2) * per_step);
   }
   if (seg_chunks > 64) seg_chunks = 64;  // the chunk-first kernel keeps a segment's slots in lanes

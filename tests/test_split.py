@@ -129,6 +129,31 @@ def test_smallest_segments(c, H, rows, prompt, seg):
     B.ca_destroy(h)
 
 
+# longer segments of a small tree pay while their length squared, times a
+# chunk's cost in 512-byte steps of 64 tokens, is below 0.8 of the run, and only
+# where the launch itself finishes the rows (schedules 2 and 3)
+@pytest.mark.parametrize("c,dt,chunks,schedule,seg", [
+    (200, B.CA_FP32, 32, 2, 1),      # a chunk costs 8: two would be 32, over 25.6
+    (200, B.CA_FP32, 80, 2, 2),
+    (200, B.CA_FP16, 80, 2, 4),
+    (256, B.CA_FP16, 63, 2, 2),
+    (64, B.CA_FP32, 100, 2, 4),
+    (64, B.CA_FP32, 250, 3, 8),
+    (64, B.CA_FP16, 64, 3, 4),
+    (64, B.CA_FP16, 64, 0, 1),
+    (64, B.CA_FP16, 64, 1, 1),
+    (16, B.CA_FP16, 64, 0, 4),       # one step of four small chunks
+])
+def test_smallest_segments_weigh_the_chain(c, dt, chunks, schedule, seg):
+    h = B.ca_create(c, 1, 128, dt, 1 << 12)
+    B.ca_set_tuning(h, schedule=schedule)
+    for sid in range(3):
+        B.ca_insert(h, sid, list(range(c * chunks)) + [100_000 + sid])
+    B.ca_workspace_size(h)
+    assert B.ca_stats(h)["seg_chunks"] == seg
+    B.ca_destroy(h)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("c,H,d,dt,prompt,lens", [
     (64, 2, 128, np.float16, 0, [64 * 6 + 1]),

@@ -257,38 +257,70 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
     run_segs[ru].second = static_cast<int32_t>(W.segs.size()) - run_segs[ru].first;
   }
 
-  // Automatic split of long private lists. One block streams a row's
-  // private chunks of one head at ~36 GB/s, so fewer blocks than compute
-  // units leave HBM idle, and a row much longer than the others ends long
-  // after them. The pieces are as long as one compute unit's share of all
-  // private steps (a step is 64 tokens), at least two steps, at most 64
-  // pieces a row; a row is cut only if that takes at least four steps off
-  // it, about what a piece's partial and the fold of one row cost. More,
-  // shorter pieces were slower: one row of 32,765 tokens (32 heads) takes 460
-  // us whole, 80 us in 8 pieces (256 blocks), 84 in 16, 88 in 32; 8,000
-  // tokens 102 / 24 us, 700 tokens 12.1 us whole and 7.6 in 6 pieces, four
-  // rows of 8,000 124 / 79 us, eight rows of 3,000 (256 blocks) 62.8 whole
-  // and 66.2 in two pieces.
-  constexpr int64_t kMinPieceSteps = 2, kMinSavedSteps = 4, kMaxPieces = 64;
+  // Automatic split of long private lists. One block streams a row's private
+  // chunks of one head as a chain of 64-token steps, so few blocks leave HBM
+  // idle, and a row much longer than the others ends long after them. The
+  // pieces are one compute unit's share of all private steps (rows x heads x
+  // tokens, whole / in pieces: fp16, 32 heads, one row of 32,765 460 / 80 us in 8,
+  // 84 in 16; 44 x 3 x 1,745, d = 64 23.2 / 16.9 in 2, 13.6 in 4). At 1,024 bytes a
+  // token they are rounded down to at most a block per compute unit, a few more
+  // of which cost a second round (86 x 1 x 2,570: 50.5 / 36.9 in 172 blocks, 46.6 in
+  // 258). They have at least two steps, four where the row's path has 8 or more
+  // segments: shorter ones end before the chunk-first blocks, which then fold all
+  // of the row's partials, four at a time (20 x 4 x 1,000 over 1,000: 18.2 / 12.4 in
+  // 4, 17.2 in 8).
+  // A row is cut only where the steps taken off it pay for the partials and the
+  // fold (32 heads, one row, whole / pieces of two steps: d = 64 6 steps 5.3 / 6.6,
+  // 10 steps 6.8 / 6.7; d = 128 6.7 / 6.9 and 8.7 / 7.1; fp32 8.8 / 7.4 at 6), and
+  // where its chain is longer than all rows' bytes take at the read rate (74 x 2 x
+  // 2,244, fp32 51.0 / 62.4 in 2; 100 x 2 x 2,000 32.2 / 34.4).
+  constexpr int64_t kMaxPieces = 64;
+  const int wide = token_head_bytes <= 256 ? 0 : token_head_bytes <= 512 ? 1 : 2;
+  const bool small = tree.chunk_size() <= 32;  // steps gathered from small chunks cost more
+  // [none, few, many segments][small][wide]
+  constexpr int kSaved[3][2][3] = {{{8, 7, 4}, {7, 5, 3}}, {{5, 5, 2}, {4, 4, 2}}, {{6, 6, 3}, {5, 4, 2}}};
+  const double step_us = (wide == 0 ? 0.65 : wide == 1 ? 0.85 : 1.16) * (small ? 1.3 : 1.0);
   const bool auto_split = split_chunks < 0 && partial_items;
   const int64_t chunk = tree.chunk_size();
-  auto steps_of = [&](int64_t chunks) { return (chunks * chunk + 63) / 64; };
+  // 64-token steps of whole chunks (a step gathers several of at most 32
+  // tokens), and of a row's private chunks as they are
+  auto steps_of = [&](int64_t chunks) {
+    return chunk <= 32 ? (chunks * chunk + 63) / 64 : chunks * ((chunk + 63) / 64);
+  };
+  std::vector<int64_t> row_steps;
+  if (auto_split) {
+    row_steps.assign(B, 0);
+    for (int64_t r = 0; r < B; ++r) {
+      if (chunk <= 32) row_steps[r] = steps_of(T.priv_ptr[r + 1] - T.priv_ptr[r]);
+      else
+        for (int32_t k = T.priv_ptr[r]; k < T.priv_ptr[r + 1]; ++k)
+          row_steps[r] += (T.node_len[T.priv_node[k]] + 63) / 64;
+    }
+  }
   int64_t piece_steps = 0;
+  double read_us = 0;  // all private bytes at the read rate
   W.split_rows = 0;
   W.grow_limit = INT32_MAX;
   if (auto_split) {
     int64_t total = 0;
-    for (int64_t r = 0; r < B; ++r) total += steps_of(T.priv_ptr[r + 1] - T.priv_ptr[r]);
+    for (int64_t st : row_steps) total += st;
     const int64_t cus = num_cus > 0 ? num_cus : 256;
-    piece_steps = std::max(kMinPieceSteps, (total * num_heads + cus - 1) / cus);
+    piece_steps = (total * num_heads + cus - 1) / cus;
+    read_us = static_cast<double>(total) * num_heads * 64 * token_head_bytes / 6.6e6;
   }
-  if (split_chunks < 0) split_chunks = 0;
-  auto pieces_of = [&](int64_t np) -> int64_t {
+  auto pieces_of = [&](int64_t r) -> int64_t {
+    const int64_t np = T.priv_ptr[r + 1] - T.priv_ptr[r];
     if (!auto_split) return split_chunks > 0 ? (np + split_chunks - 1) / split_chunks : 1;
-    const int64_t st = steps_of(np);
-    if (st < piece_steps + kMinSavedSteps) return 1;
-    return std::min({(st + piece_steps - 1) / piece_steps, kMaxPieces, np});
+    const int64_t st = row_steps[r];
+    const int64_t shared = T.shr_ptr[r + 1] - T.shr_ptr[r];
+    const int segs = shared == 0 ? 0 : shared < 8 * static_cast<int64_t>(W.seg_chunks) ? 1 : 2;
+    if (static_cast<double>(st) * step_us <= read_us + (segs ? 1.0 : 2.6)) return 1;
+    const int64_t len = std::max<int64_t>(piece_steps, segs == 2 ? 4 : 2);
+    // in whole chunks, which may save less than the steps asked for
+    const int64_t pieces = std::min({(st + (wide == 2 ? 0 : len - 1)) / len, kMaxPieces, np});
+    return pieces > 1 && st - steps_of((np + pieces - 1) / pieces) >= kSaved[segs][small][wide] ? pieces : 1;
   };
+  if (split_chunks < 0) split_chunks = 0;
 
   // Sequence-first items and per-row partial lists.
   W.items.clear();
@@ -312,7 +344,7 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
     const int32_t pe = static_cast<int32_t>(W.priv_slot.size());
     const int32_t np = pe - pb;
     const bool has_shared = static_cast<int32_t>(W.parts.size()) > W.part_ptr.back();
-    const int64_t pieces = pieces_of(np);
+    const int64_t pieces = pieces_of(r);
     if (!(partial_items && has_shared) && pieces <= 1) {
       // the row's own item produces its output directly
       W.items.push_back(SfItem{static_cast<int32_t>(r), pb, pe, -1, 0, 0, 0, 0, {}});
@@ -395,7 +427,7 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
   if (auto_split) {
     // what patches may add before the split is planned again: twice the
     // longest item, so rebuilds stay rare against the growth between them
-    int64_t most = (piece_steps + kMinSavedSteps) * 64 / chunk + 1;
+    int64_t most = (std::max<int64_t>(piece_steps, 2) + 8) * 64 / chunk + 1;
     for (const SfItem& it : W.items) most = std::max<int64_t>(most, it.ce - it.cb);
     W.grow_limit = static_cast<int32_t>(std::min<int64_t>(2 * most, INT32_MAX));
   }

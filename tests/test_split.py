@@ -30,18 +30,26 @@ def _table_cache(c, H, d, slots=1 << 16, check=False):
         os.environ.pop("CA_CHECK_PATCH", None)
 
 
-# 256 compute units: a piece is ceil(total steps * H / 256) steps, at least 2;
-# a row is cut when that takes at least 4 steps off it
+# 256 compute units: a piece is ceil(total steps * H / 256) steps, at least 2; a
+# row is cut when that takes at least 8 steps off it (d = 64, fp16, nothing
+# shared) and its chain takes longer than all bytes
 @pytest.mark.parametrize("c,H,lens,parts", [
     (64, 32, [32765], 8),            # 512 steps: pieces of 64
     (64, 32, [5 * 64], 0),           # 5 steps, pieces of 2: 3 saved, whole
-    (64, 32, [6 * 64], 3),           # 6 steps: 4 saved, 3 pieces
+    (64, 32, [6 * 64], 0),           # 6 steps: 4 saved, whole (5.3 us, 6.6 in 3 pieces)
+    (64, 32, [9 * 64], 0),           # 7 saved
+    (64, 32, [10 * 64], 5),          # 8 saved
+    (64, 64, [64 * 30] * 3, 6),      # 192 blocks: pieces of 23
+    (64, 84, [64 * 30] * 3, 0),      # 252: the chip's read rate is the limit
+    (48, 4, [250], 0),               # six chunks are six steps
     (64, 1, [64 * 512], 64),         # 256 pieces of 2 would be over the 64 a row may have
     (64, 256, [64 * 4096], 0),       # every compute unit has a whole head
     (16, 32, [32 * 64], 8),          # 128 chunks of 16 are 32 steps: pieces of 4
     (128, 32, [32 * 64], 8),         # 16 chunks of 128 likewise
     (64, 32, [64 * 300] + [64] * 8, 8),   # 308 steps: pieces of 39, the long row only
-    (300, 8, [300 * 2], 2),          # more pieces wanted than chunks
+    (300, 8, [300 * 2], 0),          # two chunks of 5 steps: 5 saved
+    (300, 8, [300 * 3], 3),          # more pieces wanted than chunks
+    (256, 8, [256 * 2 + 5], 0),      # 9 steps, not 12: three pieces save 5
 ])
 def test_plan(c, H, lens, parts):
     h = _table_cache(c, H, 64)

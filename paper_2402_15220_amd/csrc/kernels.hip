@@ -1442,28 +1442,32 @@ __global__ __launch_bounds__(256) void kkv_kernel(KvJobBatch b, const char* k, c
     }
     // 16-byte granules of K and of V, all of a pass's loads in flight before
     // its first store (a load and a store in turn waited a round trip per 4 KB:
-    // 4 chunks of 32 heads 7.0 us, now 4.2; a served batch 632 -> 588)
+    // 4 chunks of 32 heads 7.0 us, now 4.2; a served batch 632 -> 588); what is
+    // left of a pass goes granule by granule (clamped to the last one instead,
+    // 1,000 tokens in 16-token chunks took 6.2 us, 5.6 so)
     constexpr int NU = 4;
     const int total = j.n * units, shift = __builtin_ctz(units);  // 8, 16 or 32 granules a row
-    for (int i0 = threadIdx.x; i0 < total; i0 += NU * blockDim.x) {
-      u32x4 kx[NU], vx[NU];
+    const int threads = static_cast<int>(blockDim.x);
+    auto copy = [&](int i0, auto count) {
+      constexpr int N = decltype(count)::value;
+      u32x4 kx[N], vx[N];
 #pragma unroll
-      for (int e = 0; e < NU; ++e) {
-        const int i = min(i0 + e * static_cast<int>(blockDim.x), total - 1);
+      for (int e = 0; e < N; ++e) {
+        const int i = i0 + e * threads;
         const size_t so = src + (i >> shift) * stride + (i & (units - 1)) * 16;
         kx[e] = *reinterpret_cast<const u32x4*>(sk + so);
         vx[e] = *reinterpret_cast<const u32x4*>(sv + so);
       }
 #pragma unroll
-      for (int e = 0; e < NU; ++e) {
-        const int i = i0 + e * static_cast<int>(blockDim.x);
-        const size_t dof = dst + static_cast<size_t>(i) * 16;
-        if (i < total) {
-          *reinterpret_cast<u32x4*>(kpool + dof) = kx[e];
-          *reinterpret_cast<u32x4*>(vpool + dof) = vx[e];
-        }
+      for (int e = 0; e < N; ++e) {
+        const size_t dof = dst + static_cast<size_t>(i0 + e * threads) * 16;
+        *reinterpret_cast<u32x4*>(kpool + dof) = kx[e];
+        *reinterpret_cast<u32x4*>(vpool + dof) = vx[e];
       }
-    }
+    };
+    int i0 = threadIdx.x;
+    for (; i0 + (NU - 1) * threads < total; i0 += NU * threads) copy(i0, std::integral_constant<int, NU>{});
+    for (; i0 < total; i0 += threads) copy(i0, std::integral_constant<int, 1>{});
   }
   if (h == 0 && threadIdx.x == 0) slot_len[j.dst_slot] = j.kind == 2 ? j.dst_pos : j.dst_pos + j.n;
 }
@@ -1579,9 +1583,9 @@ hipError_t launch_phases(const TppParams& P, int n_sf, int schedule, int mask, h
       // place per compute unit: up to two rounds of four blocks go to the
       // kernel of their own (32 heads, fp32, d = 128, fused / own: 32 rows of 64
       // tokens 12.4 / 12.1 us, 64 of 64 22.4 / 21.7, 33 of 10 to 100 17.2 /
-      // 16.5). More rounds, and steps gathered from small chunks, stream as well
-      // or better with three (128 rows of 256 158.2 / 159.7, of 64 40.3 / 40.9; 32
-      // of 512 in 16-token chunks 78.9 / 79.9).
+      // 16.5). More rounds, and steps gathered from small chunks, do as well or
+      // better with three (128 rows of 256 158.2 / 159.7, of 64 40.3 / 40.9; 32 of 512
+      // in 16-token chunks 78.9 / 79.9, 3 of 2 in 24-token ones, 8 heads, 4.7 / 4.9).
       if constexpr (tpp_blocks_per_cu<T, D>() < 4 && !SM) {
         if (P.n_cf == 0 && n_sf <= 8 * num_cus) {
           ksf_kernel<T, D, SM><<<n_sf, 256, 0, s>>>(P.sf);

@@ -323,11 +323,14 @@ ca_status ca_stats(const ca_cache* cache, int64_t* uploads, int64_t* slots_used,
  *                is ignored. -1 keeps the current value.
  *   split_chunks private chunks per sequence-first work item; rows with more
  *                private chunks are split and their pieces merged (0
- *                disables splitting, -1 keeps the current value). Until a
- *                value is set (here or by CA_SPLIT in the environment at
- *                ca_create), schedule 2 splits by itself where rows x heads
+ *                disables splitting, -1 keeps the current value). -2, the
+ *                default unless CA_SPLIT is set in the environment at
+ *                ca_create: schedule 2 splits by itself where rows x heads
  *                alone would leave compute units idle or one row is much
- *                longer than the others; the other schedules do not.
+ *                longer than the others and the pieces pay for their
+ *                partials, up to the partials that the scratch of
+ *                ca_attention_noalloc holds (rows stay whole beyond); the
+ *                other schedules do not.
  *   phase_mask   kernels ca_attention enqueues: bit 0 chunk-first, bit 1
  *                sequence-first, bit 2 merge (0 keeps the current value; the
  *                default 7 runs all). A subset is for timing one kernel in

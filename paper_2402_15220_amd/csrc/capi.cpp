@@ -975,7 +975,7 @@ ca_status ca_export_tables(const ca_cache* cache, ca_tables* out) try {
 ca_status ca_set_tuning(ca_cache* cache, int32_t seg_chunks, int32_t split_chunks,
                         int32_t phase_mask, int32_t schedule) {
   if (!cache) return fail(CA_ERR_INVALID, "ca_set_tuning: null cache");
-  if (seg_chunks < -1 || seg_chunks > 64 || split_chunks < -1 || phase_mask < 0 || phase_mask > 7 ||
+  if (seg_chunks < -1 || seg_chunks > 64 || split_chunks < -2 || phase_mask < 0 || phase_mask > 7 ||
       schedule < -1 || schedule > 4)
     return fail(CA_ERR_INVALID, "ca_set_tuning: value out of range");
   bool rebuild = false;
@@ -989,7 +989,9 @@ ca_status ca_set_tuning(ca_cache* cache, int32_t seg_chunks, int32_t split_chunk
     cache->schedule = schedule;
     rebuild = true;
   }
-  if (split_chunks >= 0 && split_chunks != cache->split_chunks) {
+  if (split_chunks == -2) split_chunks = -1;  // automatic
+  else if (split_chunks == -1) split_chunks = cache->split_chunks;
+  if (split_chunks != cache->split_chunks) {
     cache->split_chunks = split_chunks;
     rebuild = true;
   }

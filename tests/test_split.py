@@ -60,6 +60,12 @@ def test_plan(c, H, lens, parts):
     assert B.ca_workspace_size(h) == _ws(parts, H, 64)
     B.ca_set_tuning(h, split_chunks=0)       # an explicit 0 disables it
     assert B.ca_workspace_size(h) == 0
+    B.ca_set_tuning(h, split_chunks=-1)      # kept
+    assert B.ca_workspace_size(h) == 0
+    B.ca_set_tuning(h, split_chunks=-2)      # automatic again
+    assert B.ca_workspace_size(h) == _ws(parts, H, 64)
+    with pytest.raises(B.ChunkAttnError):
+        B.ca_set_tuning(h, split_chunks=-3)
     B.ca_destroy(h)
     h = _table_cache(c, H, 64)
     B.ca_insert(h, 0, np.arange(lens[0]))

@@ -117,3 +117,40 @@ def test_units_that_end_past_the_path(c, H, d, prefix, n_q):
         q = np.random.default_rng(n).standard_normal((n, H, d)).astype(np.float16)
         o = p.cache.prefill(1, to_dev(q)).cpu().numpy()
         assert_close(o, prefill_attention(p.tree, 1, q, 1.0 / np.sqrt(d)), np.float16, f"n={n}")
+
+
+@pytest.mark.parametrize("c,d,H,n_q", [
+    (64, 64, 192, 512),    # 128-query tiles
+    (64, 128, 64, 512),
+    (16, 128, 64, 512),    # the same, four chunks a unit
+    (16, 64, 2, 70),       # 64-query tiles, two chunks a unit
+    (64, 128, 65, 250),    # 64-query tiles
+    (64, 64, 2, 70),       # 16-query blocks
+])
+def test_long_flat_tail_below_a_peak(c, d, H, n_q):
+    """One token far above a long tail whose probabilities, about 2^-16 of the
+    peak's, are subnormal in fp16: the row's sum and the product with V have to
+    treat them alike. Dropped from either side they would move o by ~0.04."""
+    print(f"[case] prefill wide flat tail c={c} d={d} H={H} n_q={n_q}", flush=True)
+    n = 3000 if H < 100 else 1500
+    rng = np.random.default_rng(d + n_q)
+    p = Pair(c, H, d, np.float16, -(-n // c) + 4)
+    k = (rng.standard_normal((n, H, d)) * 0.02).astype(np.float16)
+    k[:, :, 0] = 0
+    k[3, :, 0] = 4
+    v = (1 + 0.1 * rng.standard_normal((n, H, d))).astype(np.float16)
+    v[3] = 0
+    toks = np.arange(n, dtype=np.int32)
+    p.insert(0, toks, k, v)
+    q = (rng.standard_normal((n_q, H, d)) * 0.5).astype(np.float16)
+    q[:, :, 0] = 4
+    scale = float(np.log(2.0))  # scores in powers of two: 16 at the peak, about 0 elsewhere
+    o = p.cache.prefill(0, to_dev(q), scale=scale).cpu().numpy()
+    rows = [0, 1, 31, 32, 63, n_q - 1]
+    ref = prefill_attention(p.tree, 0, q, scale, queries=rows)
+    err = np.abs(o[rows].astype(np.float64) - ref).max()
+    print(f"[parity] flat tail max_abs={err:.3e} o={np.abs(ref).mean():.3f}", flush=True)
+    # each probability is rounded to a multiple of 2^-24, half of one at most:
+    # n of them in the sum and, times |V| < 1.5, in the product; o itself to fp16
+    assert 0.015 < np.abs(ref).mean() < 0.2
+    assert err <= 2.5 * n * 2.0 ** -25 + 2.0 ** -11 * np.abs(ref).max()

@@ -383,7 +383,7 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
   int pidx = -1;
   if (w == 0 && lane < np && np <= 64) pidx = P.parts[it.part_b + lane];
   const int len0 = !SM && n_chunks > 0 ? P.slot_len[it.slot[0]] : 0;
-  int len_lo = lane < it.n_inline ? P.slot_len[slot_lo] : 0;
+  int len_lo = !SM && lane < it.n_inline ? P.slot_len[slot_lo] : 0;
   float qf[EPL];
   E::unpack(qr, qf);
 
@@ -473,12 +473,8 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
       const int gn = min(64, n_chunks - g0);
       int slots, lens;
       if (g0 == 0) {
-        slots = slot_lo;
-        lens = len_lo;  // requested with the first rows
-        if (gn > it.n_inline && lane >= it.n_inline) {
-          slots = slot_hi;
-          lens = lane < gn ? P.slot_len[slot_hi] : 0;
-        }
+        slots = lane < it.n_inline ? slot_lo : slot_hi;
+        lens = lane < gn ? P.slot_len[slots] : 0;
       } else {
         slots = P.priv_slot[it.cb + g0 + min(lane, gn - 1)];
         lens = lane < gn ? P.slot_len[slots] : 0;
@@ -486,17 +482,19 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
       for (int j = 0; j < gn; j += G) {
         // token u is there: its chunk is in the step and in the group, and long
         // enough (an absent token reads a row of a chunk that is there)
-        bool in[U];
+        bool in[U], absent = false;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int len = __shfl(lens, min(j + min(schk[u], G - 1), gn - 1));  // all lanes take part
           in[u] = schk[u] < G && j + schk[u] < gn && srow[u] < len;
+          absent |= !in[u];
         }
         if (g0 > 0 || j > 0 || G > kSfInline) {
           load_small(slots, lens, j, gn);
-        } else {
+        } else if (__any(absent)) {
           // the first step is here already, as if its chunks were full: what an
-          // absent token's V row holds, NaN included, must not meet its 0
+          // absent token's V row holds, NaN included, must not meet its 0 (full
+          // steps don't wait for V here)
 #pragma unroll
           for (int u = 0; u < U; ++u)
             if (!in[u]) vr[u] = uint4{0, 0, 0, 0};

@@ -224,7 +224,7 @@ struct ca_cache {
         ca::build_tables(tree, &t);
         // patched lists keep the segment size of their last rebuild
         ca::build_work(tree, t, work.seg_chunks, split_rule(), schedule != 0, cfg.num_heads,
-                       num_cus, &full, schedule == 4, token_head_bytes(), counted());
+                       num_cus, &full, schedule == 4, token_head_bytes(), counted(), cfg.dtype == CA_FP32);
         const char* d = ca::same_work(work, full);
         if (*d) patch_error = std::string("work-list patch differs from a rebuild: ") + d;
       }
@@ -232,7 +232,7 @@ struct ca_cache {
       ca::build_tables(tree, &tables);
       auto rebuild = [&](int32_t split) {
         ca::build_work(tree, tables, seg_chunks, split, schedule != 0, cfg.num_heads, num_cus,
-                       &work, schedule == 4, token_head_bytes(), counted());
+                       &work, schedule == 4, token_head_bytes(), counted(), cfg.dtype == CA_FP32);
       };
       rebuild(split_rule());
       // an automatic split adds partials: not past what the static scratch
@@ -258,7 +258,7 @@ struct ca_cache {
     ca::WorkLists whole;
     ca::build_tables(tree, &tables);
     ca::build_work(tree, tables, work.seg_chunks, 0, schedule != 0, cfg.num_heads, num_cus, &whole,
-                   schedule == 4, token_head_bytes(), counted());
+                   schedule == 4, token_head_bytes(), counted(), cfg.dtype == CA_FP32);
     if (ws_bytes(whole) > limit) return false;
     work = std::move(whole);
     dw_valid = false;

@@ -137,7 +137,7 @@ void build_tables(const ChunkTree& tree, Tables* out) {
 
 void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int32_t split_chunks,
                 bool partial_items, int32_t num_heads, int32_t num_cus, WorkLists* out,
-                bool serial_reduce, int32_t token_head_bytes, bool counted) {
+                bool serial_reduce, int32_t token_head_bytes, bool counted, bool fp32) {
   WorkLists& W = *out;
   if (serial_reduce) {
     // every segment is one more launch: by default a run is one segment
@@ -278,7 +278,10 @@ void build_work(const ChunkTree& tree, const Tables& T, int32_t seg_chunks, int3
   const int wide = token_head_bytes <= 256 ? 0 : token_head_bytes <= 512 ? 1 : 2;
   const bool small = tree.chunk_size() <= 32;  // steps gathered from small chunks cost more
   // [none, few, many segments][small][wide]
-  constexpr int kSaved[3][2][3] = {{{8, 7, 4}, {7, 5, 3}}, {{5, 5, 2}, {4, 4, 2}}, {{6, 6, 3}, {5, 4, 2}}};
+  // (512 bytes are fp16 at d = 128 or fp32 at d = 64, whose chunk-first blocks end
+  // later: 4 rows, 8 heads, 1,000 shared tokens, 8 steps 9.5 / 8.8 and 8.9 / 10.0)
+  const int many = fp32 ? 7 : 4;
+  const int kSaved[3][2][3] = {{{8, 7, 4}, {7, 5, 3}}, {{5, 5, 2}, {4, 4, 2}}, {{6, many, 3}, {5, many, 2}}};
   const double step_us = (wide == 0 ? 0.65 : wide == 1 ? 0.85 : 1.16) * (small ? 1.3 : 1.0);
   const bool auto_split = split_chunks < 0 && partial_items;
   const int64_t chunk = tree.chunk_size();

@@ -87,7 +87,8 @@ void fill_item_records(WorkLists* w);
 
 void build_work(const ChunkTree& tree, const Tables& t, int32_t seg_chunks, int32_t split_chunks,
                 bool partial_items, int32_t num_heads, int32_t num_cus, WorkLists* out,
-                bool serial_reduce = false, int32_t token_head_bytes = 512, bool counted = true);
+                bool serial_reduce = false, int32_t token_head_bytes = 512, bool counted = true,
+                bool fp32 = false);
 
 // Bring work lists built for an earlier tree up to date when the only
 // structural changes since were new private chunks at the end of sequences'

@@ -860,7 +860,10 @@ ca_status ca_prefill_attention(ca_cache* cache, int64_t seq_id, const void* q, v
   // heads, 1 / 2 / 3 / 4 parts: 130 queries over 1,154 positions 19.3 / 15.7 /
   // 22.3 / 25.3 us, 300 over 1,324 22.4 / 30.6 / 27.2 / 37.3, 300 over 4,300
   // 58.1 / 64.8 / 53.7 / 65.9; rounding the parts up to a block per compute
-  // unit took 22.7, 31.1 and 66.9).
+  // unit took 22.7, 31.1 and 66.9). It is a fit for choosing between rounds, inside
+  // the limit of six units a part: there it is within 4% of the best count timed;
+  // beyond, it would ask for more parts than pay (64 queries over 1,536 positions,
+  // 4 / 6 / 8 parts: 12.7 / 11.8 / 12.5 by the model, 13.7 / 13.7 / 14.1 measured).
   const int64_t tiles = (n_q + 63) / 64 * static_cast<int64_t>(a.H);
   const int64_t units = static_cast<int64_t>(nc) * ((a.C + 63) / 64);
   int64_t split = 1;

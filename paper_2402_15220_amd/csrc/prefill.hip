@@ -600,11 +600,11 @@ typedef float float2_t __attribute__((ext_vector_type(2)));
 //     four v_readlane from a 64-chunk window held one chunk per lane;
 //   - masks use min with +-inf rather than 32 lane masks, which spilled the
 //     scalar registers.
-// Measured against the 16-query block: 2,048 queries over 8,192 positions 412
-// -> 270 us (890 TFLOP/s), 4,096 over 4,096 262 -> 175, 1,100 over 1,100 38.2
-// -> 27.2, and with 64-query tiles 2,100 over 5,100 (8 heads) 104 -> 67 and
-// 512 over 1,536 unchanged (there every block streams the whole path and the
-// 200 MB through the L2s set ~20 us).
+// Measured against the 16-query block, in 128-query tiles: 2,048 queries over
+// 8,192 positions 393 -> 267 us (900 TFLOP/s), 4,096 over 4,096 257 -> 172, 1,100
+// over 1,100 36.4 -> 27.0; in 64-query tiles: 576 over 4,000 97.7 -> 67.1, 1,100 over
+// 1,100 36.4 -> 26.0. With one 64-query block a compute unit, and so one wavefront
+// a SIMD, it is a tie (512 over 1,536 24.7 / 25.0), and the 16-query blocks stay.
 // Tried, no faster: 256-query tiles (long prefixes 5% faster, others slower),
 // three or four LDS tiles, K/V staged through registers, offsetting one half
 // of the wavefronts by half a step.

@@ -74,6 +74,25 @@ def test_plan(c, H, lens, parts):
     B.ca_destroy(h)
 
 
+# fp32, d = 128: pieces rounded down to a block per compute unit, rows cut for
+# four steps, nothing cut where all bytes take as long as the longest row
+@pytest.mark.parametrize("c,H,rows,own,prompt,parts", [
+    (128, 1, 86, 2570, 0, 172),      # 41 steps, pieces of 14: two, not three (258 blocks)
+    (64, 8, 19, 3104, 0, 0),         # 152 blocks read at the chip's rate
+    (64, 32, 1, 6 * 64, 0, 3),       # 4 steps saved
+    (64, 32, 1, 5 * 64, 0, 0),
+    (64, 8, 4, 12 * 64, 1024, 16 * 4 + 4 * 3),   # 16 segments on the path: pieces of four steps
+    (64, 8, 4, 12 * 64, 128, 2 * 4 + 4 * 6),     # 2 segments: of two
+])
+def test_plan_fp32(c, H, rows, own, prompt, parts):
+    h = B.ca_create(c, H, 128, B.CA_FP32, 1 << 13)
+    for sid in range(rows):
+        B.ca_insert(h, sid, list(range(prompt)) + list(range(100_000 * (sid + 1), 100_000 * (sid + 1) + own)))
+    B.ca_set_tuning(h, seg_chunks=1)
+    assert B.ca_workspace_size(h) == _ws(parts, H, 128)
+    B.ca_destroy(h)
+
+
 @pytest.mark.parametrize("H,rows", [(1, 1), (4, 3), (64, 5)])
 def test_growth_patches_cut_rows(H, rows):
     """Growth extends a cut row's last piece in place, each patch equal to a

@@ -469,37 +469,42 @@ __device__ __forceinline__ void ksf_block(const KsfParams& P, int item, int h, c
 
   if constexpr (SM) {
     // 64 chunks at a time, slots and lengths one per lane
-    for (int g0 = 0; g0 < n_chunks; g0 += 64) {
-      const int gn = min(64, n_chunks - g0);
-      int slots, lens;
-      if (g0 == 0) {
-        slots = lane < it.n_inline ? slot_lo : slot_hi;
-        lens = lane < gn ? P.slot_len[slots] : 0;
-      } else {
+    auto small_step = [&](int slots, int lens, int j, int gn, bool here) {
+      // token u is there: its chunk is in the step and in the group, and long
+      // enough (an absent token reads a row of a chunk that is there)
+      bool in[U], absent = false;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int len = __shfl(lens, min(j + min(schk[u], G - 1), gn - 1));  // all lanes take part
+        in[u] = schk[u] < G && j + schk[u] < gn && srow[u] < len;
+        absent |= !in[u];
+      }
+      if (!here) {
+        load_small(slots, lens, j, gn);
+      } else if (__any(absent)) {
+        // rows loaded as if the chunks were full: what an absent token's V row
+        // holds, NaN included, must not meet its 0 (full steps don't wait here)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (!in[u]) vr[u] = uint4{0, 0, 0, 0};
+      }
+      do_step(kr, vr, [&](int u) { return in[u]; });
+    };
+    int slots = lane < it.n_inline ? slot_lo : slot_hi;
+    int lens = lane < gn0 ? P.slot_len[slots] : 0;
+    int j = 0;
+    if (n_chunks > 0 && G <= kSfInline) {  // the first step, requested above
+      small_step(slots, lens, 0, gn0, true);
+      j = G;
+    }
+    for (int g0 = 0, gn = gn0; gn > 0;) {
+      for (; j < gn; j += G) small_step(slots, lens, j, gn, false);
+      g0 += 64;
+      gn = min(64, n_chunks - g0);
+      j = 0;
+      if (gn > 0) {
         slots = P.priv_slot[it.cb + g0 + min(lane, gn - 1)];
         lens = lane < gn ? P.slot_len[slots] : 0;
-      }
-      for (int j = 0; j < gn; j += G) {
-        // token u is there: its chunk is in the step and in the group, and long
-        // enough (an absent token reads a row of a chunk that is there)
-        bool in[U], absent = false;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int len = __shfl(lens, min(j + min(schk[u], G - 1), gn - 1));  // all lanes take part
-          in[u] = schk[u] < G && j + schk[u] < gn && srow[u] < len;
-          absent |= !in[u];
-        }
-        if (g0 > 0 || j > 0 || G > kSfInline) {
-          load_small(slots, lens, j, gn);
-        } else if (__any(absent)) {
-          // the first step is here already, as if its chunks were full: what an
-          // absent token's V row holds, NaN included, must not meet its 0 (full
-          // steps don't wait for V here)
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-            if (!in[u]) vr[u] = uint4{0, 0, 0, 0};
-        }
-        do_step(kr, vr, [&](int u) { return in[u]; });
       }
     }
   }
@@ -1558,9 +1563,10 @@ __global__ __launch_bounds__(256 * kDeepChains) void kcf_deep_kernel(KcfParams P
     kcf_f32_block<SM, D, 1, float, kDeepChains>(P, rest / zb, rest % zb, h, lds);
 }
 
-// (fp32, d = 128 is capped for the four blocks the fused kernel has no room for)
+// (fp32, d = 128 is capped for the four blocks the fused kernel has no room for;
+// with steps gathered from small chunks the cap costs 8%)
 template <typename T, int D, bool SM>
-__global__ __launch_bounds__(256, (tpp_blocks_per_cu<T, D>() < 4 ? 4 : 1)) void ksf_kernel(KsfParams P) {
+__global__ __launch_bounds__(256, (tpp_blocks_per_cu<T, D>() < 4 && !SM ? 4 : 1)) void ksf_kernel(KsfParams P) {
   __shared__ __attribute__((aligned(16))) char lds[ksf_lds_bytes<T, D>()];
   const int b = static_cast<int>(blockIdx.x);
   ksf_block<T, D, SM>(P, b / P.H, b % P.H, lds);

@@ -1445,32 +1445,37 @@ __global__ __launch_bounds__(256) void kkv_kernel(KvJobBatch b, const char* k, c
     }
     // 16-byte granules of K and of V, all of a pass's loads in flight before
     // its first store (a load and a store in turn waited a round trip per 4 KB:
-    // 4 chunks of 32 heads 7.0 us, now 4.2; a served batch 632 -> 588); what is
-    // left of a pass goes granule by granule (clamped to the last one instead,
-    // 1,000 tokens in 16-token chunks took 6.2 us, 5.6 so)
+    // 4 chunks of 32 heads 7.0 us, now 4.2; a served batch 632 -> 588); the last
+    // pass loads only what is there (places past the end clamped to the last
+    // granule: 1,000 tokens in 16-token chunks 6.2 us, 5.6 so)
     constexpr int NU = 4;
     const int total = j.n * units, shift = __builtin_ctz(units);  // 8, 16 or 32 granules a row
     const int threads = static_cast<int>(blockDim.x);
-    auto copy = [&](int i0, auto count) {
-      constexpr int N = decltype(count)::value;
-      u32x4 kx[N], vx[N];
+    auto pass = [&](int i0, auto all) {
+      constexpr bool whole = decltype(all)::value;
+      u32x4 kx[NU], vx[NU];
 #pragma unroll
-      for (int e = 0; e < N; ++e) {
+      for (int e = 0; e < NU; ++e) {
         const int i = i0 + e * threads;
-        const size_t so = src + (i >> shift) * stride + (i & (units - 1)) * 16;
-        kx[e] = *reinterpret_cast<const u32x4*>(sk + so);
-        vx[e] = *reinterpret_cast<const u32x4*>(sv + so);
+        if (whole || i < total) {
+          const size_t so = src + (i >> shift) * stride + (i & (units - 1)) * 16;
+          kx[e] = *reinterpret_cast<const u32x4*>(sk + so);
+          vx[e] = *reinterpret_cast<const u32x4*>(sv + so);
+        }
       }
 #pragma unroll
-      for (int e = 0; e < N; ++e) {
-        const size_t dof = dst + static_cast<size_t>(i0 + e * threads) * 16;
-        *reinterpret_cast<u32x4*>(kpool + dof) = kx[e];
-        *reinterpret_cast<u32x4*>(vpool + dof) = vx[e];
+      for (int e = 0; e < NU; ++e) {
+        const int i = i0 + e * threads;
+        if (whole || i < total) {
+          const size_t dof = dst + static_cast<size_t>(i) * 16;
+          *reinterpret_cast<u32x4*>(kpool + dof) = kx[e];
+          *reinterpret_cast<u32x4*>(vpool + dof) = vx[e];
+        }
       }
     };
     int i0 = threadIdx.x;
-    for (; i0 + (NU - 1) * threads < total; i0 += NU * threads) copy(i0, std::integral_constant<int, NU>{});
-    for (; i0 < total; i0 += threads) copy(i0, std::integral_constant<int, 1>{});
+    for (; i0 + (NU - 1) * threads < total; i0 += NU * threads) pass(i0, std::true_type{});
+    if (i0 < total) pass(i0, std::false_type{});
   }
   if (h == 0 && threadIdx.x == 0) slot_len[j.dst_slot] = j.kind == 2 ? j.dst_pos : j.dst_pos + j.n;
 }

@@ -265,8 +265,8 @@ struct KsfParams {
   int C;
   float qscale;
   int32_t* cnt;  // partial-writing schedules: per (row, head) arrival counters, else null
-  const int32_t* row_map;  // tree row -> row of q and o (null: tree order)
   int cnt_layout;  // see counter_layout()
+  const int32_t* row_map;  // tree row -> row of q and o (null: tree order)
 };
 
 // Lane layout: a token row of d elements is read by LPT = d/EPL lanes, 16
@@ -642,12 +642,12 @@ struct KcfParams {
   // partial-writing schedules only (null otherwise): per (row, head) arrival counters
   // and what the last contributor needs to finish the row
   int32_t* cnt;
+  int cnt_layout;  // see counter_layout()
   void* o;
   const int32_t* part_ptr;
   const int32_t* parts;
   const int32_t* row_map;  // tree row -> row of q and o (null: tree order)
   int seg_base;            // index in the whole segment list of segs[0]
-  int cnt_layout;          // see counter_layout()
 };
 
 // The block index, after the arguments a chunk-first block reads first: left to
@@ -655,7 +655,7 @@ struct KcfParams {
 // apart, which a short call sees as 0.2 us.
 __device__ __forceinline__ int block_index(const KcfParams& P) {
   int b = static_cast<int>(blockIdx.x);
-  asm("" : "+s"(b) : "s"(P.slot_len), "s"(P.segs), "s"(P.seg_slots));
+  asm("" : "+s"(b) : "s"(P.slot_len), "s"(P.segs), "s"(P.seg_slots), "s"(P.C));
   return b;
 }
 
@@ -894,9 +894,9 @@ __device__ __forceinline__ void cf_publish(const KcfParams& P, const CfSeg& sg, 
 // takes 16 tokens, so chunks of up to 16 tokens go one to a wavefront, of up
 // to 32 one to a pair; with longer ones the four share each chunk. (One
 // 16-token chunk per chain left three of four wavefronts idle: 32 identical
-// sequences of 2,048 tokens took 21 us so, 12.4 us now.) Kernels for longer
+// sequences of 2,048 tokens took 21 us so, 12.4 us now.) fp16 kernels for longer
 // chunks (SM false) have the 1 as a constant: with a count known only at run
-// time their chains took 5% longer (two rows over 4,771 tokens, 2 heads).
+// time their chains took 1 to 2% longer (two rows over 4,771 tokens, 2 heads).
 __device__ __forceinline__ int chunks_at_once(int C) { return C <= 16 ? 4 : C <= 32 ? 2 : 1; }
 
 // Lazy reference maximum of the chunk-first softmax (log2 units): P <= 2^8.
@@ -1223,7 +1223,7 @@ __device__ __forceinline__ void kcf_f32_block(const KcfParams& P, int seg, int z
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // chain (wave-uniform): takes chunks chain, chain + stride, ...; wq: this
   // wavefront's 16-token slice of them
-  const int at_once = SM ? chunks_at_once(P.C) : 1, stride = NCH * at_once;
+  const int at_once = chunks_at_once(P.C), stride = NCH * at_once;  // (a constant for long chunks gains nothing here)
   const int wpc = 4 / at_once;
   const int chain = __builtin_amdgcn_readfirstlane((w >> 2) * at_once + (w & 3) / wpc);
   const int wq = (w & 3) % wpc;
@@ -1518,8 +1518,9 @@ __global__ __launch_bounds__(256, (tpp_blocks_per_cu<T, D>())) void tpp_kernel(T
   const int b = static_cast<int>(blockIdx.x);
   const int H = P.sf.H;
   if (b < P.n_cf) {
-    const int h = b % H;
-    const int rest = b / H;
+    const int cb = block_index(P.cf);
+    const int h = cb % H;
+    const int rest = cb / H;
     const int z = rest % P.zb;
     const int seg = rest / P.zb;
     if constexpr (sizeof(T) == 2)
@@ -1654,10 +1655,10 @@ hipError_t launch_all(const AttnArgs& a, const DevWork& w, hipStream_t s, int ma
   const bool counting = w.schedule == 2 || w.schedule == 3;  // the last contributor finishes each row
   P.cf = KcfParams{a.q, a.kpool, a.vpool, a.ss, a.hs, a.slot_len, w.segs, w.seg_slots, a.ws_o,
                    reinterpret_cast<float2*>(a.ws_ml), a.ws_o_bytes, a.H, a.C, a.qscale,
-                   counting ? a.cnt : nullptr, a.o, w.part_ptr, w.parts, a.row_map, 0, a.cnt_layout};
+                   counting ? a.cnt : nullptr, a.cnt_layout, a.o, w.part_ptr, w.parts, a.row_map, 0};
   P.sf = KsfParams{a.q, a.o, a.kpool, a.vpool, a.ss, a.hs, a.slot_len, w.items, w.priv_slot, w.part_ptr,
                    w.parts, a.ws_o, reinterpret_cast<float2*>(a.ws_ml), a.ws_o_bytes, a.H, a.C,
-                   a.qscale, counting ? a.cnt : nullptr, a.row_map, a.cnt_layout};
+                   a.qscale, counting ? a.cnt : nullptr, a.cnt_layout, a.row_map};
   // At most 16 or 32 covered rows per chunk-first block; wider runs take
   // several row blocks, which re-read the chunk. Their block indices differ
   // by a multiple of H, so for H a multiple of 8 they land on the same XCD
